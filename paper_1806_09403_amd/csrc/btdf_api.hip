@@ -775,7 +775,6 @@ int enqueue_step(btdf_t *h, const LbmParams &p, const IbParams &ib, int src, hip
   if (te) HIPCHK(hipEventRecord(te->ib1, s));
   HIPCHK(launch_lbm(h->prec, h->variant, A, B, p, TileRange{nullptr, 0, h->ntx * h->nty, 1}, ib, s));
   if (te) HIPCHK(hipEventRecord(te->a1, s));
-  if (p.outlet == 2) HIPCHK(launch_conv_outlet(h->prec, A, B, p, s));
   // moving bodies advance after the step that used their positions (the body
   // reduction in the lattice launch reads the centres)
   if (h->any_moving()) HIPCHK(launch_rigid_move(make_move(h), s));
@@ -1266,12 +1265,10 @@ static int enqueue_pair(btdf_t *h, const LbmParams &p, const IbParams &ib, hipSt
   if (ev && ev[6]) HIPCHK(hipEventRecord(ev[6], s));
   const int nb0 = h->n_groups();  // the near tiles start here in the map
   HIPCHK(launch_lbm(h->prec, h->variant, A, X, p, TileRange{fm, nb0, h->n_near, 1}, ib, s));
-  if (p.outlet == 2) HIPCHK(launch_conv_outlet(h->prec, A, X, p, s));
   if (ev && ev[2]) HIPCHK(hipEventRecord(ev[2], s));
   HIPCHK(launch_ib(h->prec, X, p, ib, s));
   if (ev && ev[3]) HIPCHK(hipEventRecord(ev[3], s));
   HIPCHK(launch_lbm(h->prec, h->variant, X, B, p, TileRange{fm, nb0, h->n_near, 1}, ib, s));
-  if (p.outlet == 2) HIPCHK(launch_conv_outlet(h->prec, X, B, p, s));
   if (ev && ev[4]) HIPCHK(hipEventRecord(ev[4], s));
   h->cur ^= 1;
   h->steps += 2;
@@ -1309,7 +1306,6 @@ static int enqueue_triple(btdf_t *h, const LbmParams &p, const IbParams &ib, hip
   HIPCHK(launch_ib(h->prec, A, p, ib, s));
   if (ev && ev[1]) HIPCHK(hipEventRecord(ev[1], s));
   HIPCHK(launch_lbm(h->prec, h->variant, A, X1, p, TileRange{fm, nb0, h->n_near, 1}, ib, s));
-  if (p.outlet == 2) HIPCHK(launch_conv_outlet(h->prec, A, X1, p, s));
   if (ev && ev[2]) HIPCHK(hipEventRecord(ev[2], s));
   // the pass: the smallest groups (which border near tiles) first, the
   // largest last; every launch but the largest interior groups' on a second
@@ -1337,12 +1333,10 @@ static int enqueue_triple(btdf_t *h, const LbmParams &p, const IbParams &ib, hip
   HIPCHK(launch_ib(h->prec, X1, p, ib, s));
   if (ev && ev[3]) HIPCHK(hipEventRecord(ev[3], s));
   HIPCHK(launch_lbm(h->prec, h->variant, X1, X2, p, TileRange{fm, nb0, h->n_near, 1}, ib, s));
-  if (p.outlet == 2) HIPCHK(launch_conv_outlet(h->prec, X1, X2, p, s));
   if (ev && ev[4]) HIPCHK(hipEventRecord(ev[4], s));
   HIPCHK(launch_ib(h->prec, X2, p, ib, s));
   if (ev && ev[7]) HIPCHK(hipEventRecord(ev[7], s));
   HIPCHK(launch_lbm(h->prec, h->variant, X2, B, p, TileRange{fm, nb0, h->n_near, 1}, ib, s));
-  if (p.outlet == 2) HIPCHK(launch_conv_outlet(h->prec, X2, B, p, s));
   if (ev && ev[8]) HIPCHK(hipEventRecord(ev[8], s));
   h->cur ^= 1;
   h->steps += 3;
@@ -1368,7 +1362,6 @@ static int enqueue_deep(btdf_t *h, const LbmParams &p, const IbParams &ib, hipSt
   HIPCHK(launch_ib(h->prec, A, p, ib, s));
   HIPCHK(mark(1));
   HIPCHK(launch_lbm(h->prec, h->variant, A, X[1], p, TileRange{fm, nb0, h->n_near, 1}, ib, s));
-  if (p.outlet == 2) HIPCHK(launch_conv_outlet(h->prec, A, X[1], p, s));
   HIPCHK(mark(2));
   // the pass: the smaller groups' launches on a second stream, beside the
   // largest groups' launch (they are one to three waves of workgroups long,
@@ -1398,8 +1391,7 @@ static int enqueue_deep(btdf_t *h, const LbmParams &p, const IbParams &ib, hipSt
     HIPCHK(launch_ib(h->prec, X[k], p, ib, s));
     HIPCHK(mark(2 * k + 2));
     HIPCHK(launch_lbm(h->prec, h->variant, X[k], dst, p, TileRange{fm, nb0, h->n_near, 1}, ib, s));
-    if (p.outlet == 2) HIPCHK(launch_conv_outlet(h->prec, X[k], dst, p, s));
-    HIPCHK(mark(2 * k + 3));
+      HIPCHK(mark(2 * k + 3));
   }
   h->cur ^= 1;
   h->steps += d;

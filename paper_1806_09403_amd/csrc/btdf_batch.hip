@@ -250,12 +250,6 @@ struct BatchEvents {
   hipEvent_t e0, e1, e2;
 };
 
-bool batch_has_conv(const btdf_batch_t *b) {
-  bool conv = false;
-  for (const btdf_t *c : b->cases) conv |= c->bc[1] == BTDF_CONVECTIVE_OUTLET;
-  return conv;
-}
-
 int batch_enqueue(btdf_batch_t *b, int parity, hipStream_t s, const BatchEvents *te) {
   const CaseDesc *desc = reinterpret_cast<const CaseDesc *>(b->ws + b->off_desc);
   const int rt = route(parity, parity ^ 1);
@@ -264,7 +258,6 @@ int batch_enqueue(btdf_batch_t *b, int parity, hipStream_t s, const BatchEvents 
   if (te) HIPCHK(hipEventRecord(te->e1, s));
   HIPCHK(launch_lbm_batch(b->prec, b->variant, desc, b->map, rt, s));
   if (te) HIPCHK(hipEventRecord(te->e2, s));
-  if (batch_has_conv(b)) HIPCHK(launch_conv_outlet_batch(b->prec, desc, (int)b->cases.size(), b->mask, rt, s));
   return ok();
 }
 
@@ -277,12 +270,10 @@ int batch_enqueue(btdf_batch_t *b, int parity, hipStream_t s, const BatchEvents 
 // near steps (e1-e2, e5-e6, e7-e8 in the pairs listed).
 int batch_enqueue_triple(btdf_batch_t *b, int parity, hipStream_t s, hipEvent_t *ev) {
   const CaseDesc *desc = reinterpret_cast<const CaseDesc *>(b->ws + b->off_desc);
-  const int A = parity, B = parity ^ 1, K = (int)b->cases.size();
-  const bool conv = batch_has_conv(b);
+  const int A = parity, B = parity ^ 1;
   auto rec = [&](int i) -> hipError_t { return ev ? hipEventRecord(ev[i], s) : hipSuccess; };
   auto near_step = [&](int src, int dst) -> int {
     HIPCHK(launch_lbm_batch(b->prec, b->variant, desc, b->map_near, route(src, dst), s));
-    if (conv) HIPCHK(launch_conv_outlet_batch(b->prec, desc, K, b->mask, route(src, dst), s));
     return ok();
   };
   int rc;

@@ -463,12 +463,12 @@ __device__ __forceinline__ unsigned long long bad_lanes(T rho) {
 // column 1's density. As stored deviations, feq_q(1 + dr, u_in) - c_q =
 // w (dr a_q + b_q) with a_q = 1 + P(u_in), b_q = P(u_in) - P(u_ref), P(u) =
 // 3 e.u + 4.5 (e.u)^2 - 1.5 |u|^2, and dr the sum of column 1's
-// post-collision deviations (inlet_dr). The single-step kernels form a and b
-// in FP64 as they go (inlet_ghost_calc); the edge kernels of the blocked
-// pass read them, and the wall shifts of pull(), from a table the host
-// fills once (fill_konst, kernel parameter konst). Both take the same FP64
-// operations in the same order without contraction, so they agree bit for
-// bit.
+// post-collision deviations (inlet_dr). Every kernel reads a and b, and the
+// edge kernels the wall shifts of pull(), from a table the host fills once
+// (fill_konst, kernel parameter konst): formed in the lane that writes the
+// ghost they are nine FP64 divisions in a row, which made the whole launch
+// wait (a 200x120 channel without bodies took 6.15 us a step against 4.13
+// for the periodic lattice, FP32, graph replay).
 template <typename T>
 __device__ __forceinline__ T inlet_dr(const T (&out)[9]) {
   T dr = out[0];
@@ -488,12 +488,6 @@ __host__ __device__ __forceinline__ double inlet_b(const LbmParams &p, int q) {
   const double ein = ex(q) * p.uin_x + ey(q) * p.uin_y;
   const double pin = 3.0 * ein + 4.5 * ein * ein - 1.5 * (p.uin_x * p.uin_x + p.uin_y * p.uin_y);
   return pin - (ref_c(q, p.urx, p.ury) / wq(q) - 1.0);
-}
-
-template <typename T>
-__device__ __forceinline__ T inlet_ghost_calc(T dr, const LbmParams &p, int q) {
-#pragma clang fp contract(off)
-  return (T)wq(q) * (dr * (T)inlet_a(p, q) + (T)inlet_b(p, q));
 }
 
 // the shift of a population pulled from beyond a halfway bounce-back wall
@@ -536,8 +530,10 @@ __device__ __forceinline__ const T *konst(const LbmParams &p) {
 template <typename T>
 __device__ __forceinline__ T inlet_ghost(T dr, const LbmParams &p, int q) {
 #pragma clang fp contract(off)
-  const T *k = konst<T>(p);
-  return (T)wq(q) * (dr * ldg(k, q) + ldg(k, 9 + q));
+  // (read-only for the whole launch: constant memory, so a uniform table
+  // comes through scalar loads and costs no vector registers)
+  const __attribute__((address_space(4))) T *k = (const __attribute__((address_space(4))) T *)konst<T>(p);
+  return (T)wq(q) * (dr * k[q] + k[9 + q]);
 }
 
 // Streaming pull g_q(x, y) = f_q(x - e_q, y - e_q), as a stored deviation,

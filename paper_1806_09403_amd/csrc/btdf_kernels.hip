@@ -288,6 +288,26 @@ __device__ __forceinline__ int stop_flag(const int *stop) {
   return 0;
 }
 
+// Convective outlet (d/dt + U d/dx = 0 on the ghost column, implicit upwind):
+// the ghost of B is (ghost of A + U column nx-2 of B) / (1 + U), written by
+// the lane that has just made column nx-2 (base: its offset, out: its
+// values). The reference offsets of the stored deviations cancel (the
+// weights sum to one).
+template <typename T>
+__device__ __forceinline__ void conv_outlet_node(const T *__restrict__ A, T *__restrict__ B, const LbmParams &p,
+                                                 long long base, const T (&out)[9]) {
+  const T U = (T)p.uconv, den = (T)(1.0 + p.uconv);
+  T g[9];
+  __builtin_amdgcn_sched_barrier(0);  // (no earlier: the loads' registers would add to the collision's)
+#pragma unroll
+  for (int q = 0; q < 9; ++q) g[q] = load<T>(&A[(long long)q * p.plane + base + 1]);
+#pragma unroll
+  for (int q = 0; q < 9; ++q) {
+    B[(long long)q * p.plane + base + 1] = (g[q] + U * out[q]) / den;
+    __builtin_amdgcn_sched_barrier(0);  // one division's temporaries at a time
+  }
+}
+
 // one tile t of the lattice: streaming pull, spread gather, collision; with
 // STOP and *stop set, nothing is stored (a stopped batch case)
 template <typename T, int BX, int BY, int NPT, bool NT, bool NTL, bool STOP = false>
@@ -414,11 +434,15 @@ __device__ __forceinline__ void lbm_tile(const T *__restrict__ A, T *__restrict_
       const T dr = inlet_dr<T>(out);
       const long long gb = (long long)y * p.pitch;
 #pragma unroll
-      for (int q = 0; q < 9; ++q) B[(long long)q * p.plane + gb] = inlet_ghost_calc<T>(dr, p, q);
+      for (int q = 0; q < 9; ++q) B[(long long)q * p.plane + gb] = inlet_ghost<T>(dr, p, q);
     }
-    if (p.outlet == 1 && x == p.nx - 2) {
+    if (p.outlet && x == p.nx - 2) {
+      if (p.outlet == 1) {
 #pragma unroll
-      for (int q = 0; q < 9; ++q) B[(long long)q * p.plane + base + 1] = out[q];
+        for (int q = 0; q < 9; ++q) B[(long long)q * p.plane + base + 1] = out[q];
+      } else {
+        conv_outlet_node<T>(A, B, p, base, out);
+      }
     }
   }
   if (bad) p.flag[0] = -1;
@@ -1200,58 +1224,6 @@ hipError_t launch_ib_batch(int prec, const CaseDesc *cases, const BatchMap &m, i
     hipLaunchKernelGGL(ib_batch_kernel<float>, dim3(m.nmblk), dim3(256), 0, s, cases, m, rt);
   else
     hipLaunchKernelGGL(ib_batch_kernel<double>, dim3(m.nmblk), dim3(256), 0, s, cases, m, rt);
-  return hipGetLastError();
-}
-
-// Convective outlet (d/dt + U d/dx = 0 on the ghost column, implicit
-// upwind): after the lattice kernel has written column nx-2 of B, the ghost
-// of B is (ghost of A + U column nx-2 of B) / (1 + U). The reference
-// offsets of the stored deviations cancel (the weights sum to one). Kept
-// out of the lattice kernel, where it cost registers on every node.
-template <typename T>
-__device__ __forceinline__ void conv_outlet_row(const T *__restrict__ A, T *__restrict__ B, const LbmParams &p,
-                                                int y) {
-  const T U = (T)p.uconv, den = (T)(1.0 + p.uconv);
-  const long long base = (long long)y * p.pitch + p.nx - 2;
-#pragma unroll
-  for (int q = 0; q < 9; ++q) {
-    const long long o = (long long)q * p.plane + base;
-    B[o + 1] = (A[o + 1] + U * B[o]) / den;
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void conv_outlet_kernel(const T *__restrict__ A, T *__restrict__ B, LbmParams p) {
-  const int y = (int)blockIdx.x * 256 + (int)threadIdx.x;
-  if (y < p.ny) conv_outlet_row<T>(A, B, p, y);
-}
-
-// batches: one workgroup per case, cases without a convective outlet (or stopped) return
-template <typename T>
-__global__ __launch_bounds__(256) void conv_outlet_batch_kernel(const CaseDesc *__restrict__ cases, int mask_unstable,
-                                                                int rt) {
-  const CaseDesc &cd = cases[blockIdx.x];
-  if (cd.p.outlet != 2 || (mask_unstable && cd.p.flag[0] != 0)) return;
-  const T *A = reinterpret_cast<const T *>(cd.pop[route_src(rt)]);
-  T *B = reinterpret_cast<T *>(cd.pop[route_dst(rt)]);
-  for (int y = (int)threadIdx.x; y < cd.p.ny; y += 256) conv_outlet_row<T>(A, B, cd.p, y);
-}
-
-hipError_t launch_conv_outlet(int prec, const void *A, void *B, const LbmParams &p, hipStream_t s) {
-  const int blocks = (p.ny + 255) / 256;
-  if (prec == 4)
-    hipLaunchKernelGGL(conv_outlet_kernel<float>, dim3(blocks), dim3(256), 0, s, (const float *)A, (float *)B, p);
-  else
-    hipLaunchKernelGGL(conv_outlet_kernel<double>, dim3(blocks), dim3(256), 0, s, (const double *)A, (double *)B, p);
-  return hipGetLastError();
-}
-
-hipError_t launch_conv_outlet_batch(int prec, const CaseDesc *cases, int ncases, int mask_unstable, int rt,
-                                    hipStream_t s) {
-  if (prec == 4)
-    hipLaunchKernelGGL(conv_outlet_batch_kernel<float>, dim3(ncases), dim3(256), 0, s, cases, mask_unstable, rt);
-  else
-    hipLaunchKernelGGL(conv_outlet_batch_kernel<double>, dim3(ncases), dim3(256), 0, s, cases, mask_unstable, rt);
   return hipGetLastError();
 }
 

@@ -71,9 +71,6 @@ bool variant_has_deep(int variant, int prec, int depth, int code);
 hipError_t launch_lbm_deep(int prec, int variant, int depth, int code, const void *A, void *C, const LbmParams &p,
                            const int *map, int count, int ring_groups, void *ring, const unsigned *rwin,
                            hipStream_t s);
-hipError_t launch_conv_outlet(int prec, const void *A, void *B, const LbmParams &p, hipStream_t s);
-hipError_t launch_conv_outlet_batch(int prec, const CaseDesc *cases, int ncases, int mask_unstable, int rt,
-                                    hipStream_t s);
 hipError_t launch_marker_velocity(int prec, const void *A, const LbmParams &p, const IbParams &ib,
                                   const int *cover_off, const int *cover_list, double *out, hipStream_t s);
 hipError_t launch_marker_velocity_tiles(int prec, const void *A, const LbmParams &p, const IbParams &ib, int tile_x,
