@@ -288,11 +288,81 @@ __device__ __forceinline__ int stop_flag(const int *stop) {
   return 0;
 }
 
+// The spread force of the cnt markers staged in LDS (stencil origins, then
+// wx[4], wy[4], drs ds F_x, drs ds F_y) on this thread's nodes (xb + k BX, y),
+// added in ascending marker order. Each lane first tests one marker against
+// the rows of its wave (WR rows from yw); the wave then walks the set bits of
+// that mask, four markers at a time with their LDS reads in flight together,
+// and each lane keeps the sums of the markers whose stencil covers its node.
+// A loop over all markers with a branch per marker instead waited for two
+// dependent LDS reads per marker (200x120 FP64 channel, 50 markers: 13.3 us a
+// step then, 12.4 now; 2000x800 FP32 shedding: 28.6 and 26.2).
+template <typename T, int BX, int NPT, int WR>
+__device__ __forceinline__ void spread_gather(const int (&s_ix)[kChunk], const int (&s_iy)[kChunk],
+                                              const T (&s_w)[kChunk][10], int cnt, int S, const LbmParams &p, int xb,
+                                              int y, int yw, T (&fx)[NPT], T (&fy)[NPT]) {
+  static_assert(kChunk <= 64, "one marker per lane of a wave");
+  const int lane = (int)(threadIdx.y * BX + threadIdx.x) & 63;
+  // rows yw .. yw + WR - 1 meet rows iy .. iy + S - 1 (mod ny) if e < S + WR - 1
+  int e = yw + WR - 1 - s_iy[lane < cnt ? lane : 0];
+  if (p.yper && e < 0) e += p.ny;
+  unsigned long long m = __builtin_amdgcn_ballot_w64(lane < cnt && (unsigned)e < (unsigned)(S + WR - 1));
+  while (m) {
+    int id[4];
+    bool on[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      on[u] = m != 0;
+      id[u] = on[u] ? __builtin_ctzll(m) : id[u ? u - 1 : 0];
+      m &= m - 1;
+    }
+    int dy[4];
+    T wy[4], Fx[4], Fy[4];
+    int ix[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      dy[u] = y - s_iy[id[u]];
+      ix[u] = s_ix[id[u]];
+      Fx[u] = s_w[id[u]][8];
+      Fy[u] = s_w[id[u]][9];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (p.yper && dy[u] < 0) dy[u] += p.ny;
+      on[u] = on[u] && (unsigned)dy[u] < (unsigned)S;
+      wy[u] = s_w[id[u]][4 + (dy[u] & 3)];
+    }
+#pragma unroll
+    for (int k = 0; k < NPT; ++k) {
+      int dx[4];
+      T wx[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        dx[u] = xb + k * BX - ix[u];
+        if (p.xper && dx[u] < 0) dx[u] += p.nx;
+        wx[u] = s_w[id[u]][dx[u] & 3];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const T W = wx[u] * wy[u];
+        const T ax = fmx(W, Fx[u], fx[k]), ay = fmx(W, Fy[u], fy[k]);
+        const bool in = on[u] && (unsigned)dx[u] < (unsigned)S;
+        fx[k] = in ? ax : fx[k];
+        fy[k] = in ? ay : fy[k];
+      }
+    }
+  }
+}
+
 // Convective outlet (d/dt + U d/dx = 0 on the ghost column, implicit upwind):
 // the ghost of B is (ghost of A + U column nx-2 of B) / (1 + U), written by
 // the lane that has just made column nx-2 (base: its offset, out: its
 // values). The reference offsets of the stored deviations cancel (the
-// weights sum to one).
+// weights sum to one). Here it costs nothing measurable: as a launch after
+// the step it was one round trip per population on one thread per row, 9.8
+// us at 401 rows and 15.3 us at 1601 (the 1601^2 far-field run: 49.5 us a
+// step then, 33.0 now). The loads stay behind the collision so that the
+// kernel's registers are the collision's.
 template <typename T>
 __device__ __forceinline__ void conv_outlet_node(const T *__restrict__ A, T *__restrict__ B, const LbmParams &p,
                                                  long long base, const T (&out)[9]) {
@@ -382,23 +452,7 @@ __device__ __forceinline__ void lbm_tile(const T *__restrict__ A, T *__restrict_
         for (int k = 0; k < 10; ++k) s_w[tid][k] = ldg(mw, 10 * (long long)l + k);
       }
       __syncthreads();
-      for (int e = 0; e < cnt; ++e) {
-        int dy = y - s_iy[e];
-        if (p.yper && dy < 0) dy += p.ny;
-        if ((unsigned)dy < (unsigned)S) {
-          const T wyv = s_w[e][4 + dy];
-#pragma unroll
-          for (int k = 0; k < NPT; ++k) {
-            int dx = xb + k * BX - s_ix[e];
-            if (p.xper && dx < 0) dx += p.nx;
-            if ((unsigned)dx < (unsigned)S) {
-              const T W = s_w[e][dx] * wyv;
-              fib_x[k] += W * s_w[e][8];
-              fib_y[k] += W * s_w[e][9];
-            }
-          }
-        }
-      }
+      spread_gather<T, BX, NPT, WR>(s_ix, s_iy, s_w, cnt, S, p, xb, y, yw, fib_x, fib_y);
     }
   }
   if (y >= p.ny || halt) return;  // (after the gather's last barrier)
