@@ -192,14 +192,19 @@ int reverse_step(const Adj &X, const void *A, int64_t k, const double *hbar, int
 // marker record (records set * K + k)
 int recompute_segment(const Adj &X, int set, int64_t len, hipStream_t s) {
   const int prec = X.h->prec;
+  const TileRange all{nullptr, 0, X.nt, 0};  // (neither the step counter nor the body forces)
+  const bool one = one_launch(X.h, false);
   for (int64_t k = 0; k < len; ++k) {
     LbmParams pk;
     IbParams ik;
     X.slot_params(set * X.L->K + k, X.pa, X.iba, &pk, &ik);
-    HIPCHK(launch_ib(prec, X.seg(set, k), pk, ik, s));
-    if (k + 1 < len)
-      HIPCHK(launch_lbm(prec, X.h->variant, X.seg(set, k), X.seg(set, k + 1), pk, TileRange{nullptr, 0, X.nt, 0},
-                        ik, s));
+    if (!one || k + 1 == len) HIPCHK(launch_ib(prec, X.seg(set, k), pk, ik, s));
+    if (k + 1 == len) break;
+    if (one)
+      HIPCHK(launch_step(prec, X.seg(set, k), X.seg(set, k + 1), pk, step_work(X.h, false), ik,
+                         StepLink{nullptr, nullptr, 0, 0, 1, 0}, s));
+    else
+      HIPCHK(launch_lbm(prec, X.h->variant, X.seg(set, k), X.seg(set, k + 1), pk, all, ik, s));
   }
   return ok();
 }
@@ -219,12 +224,13 @@ int reverse_segment(const Adj &X, int set, int64_t len, int gi, hipStream_t s) {
 
 // K forward steps of the handle from its buffer c, on stream s
 int forward_steps(const Adj &X, int64_t len, int c, hipStream_t s) {
+  StepRun run{len};
   for (int64_t k = 0; k < len; ++k) {
-    int rc = enqueue_step(X.h, X.p, X.ib, c, s, nullptr);
+    int rc = enqueue_step(X.h, X.p, X.ib, c, s, nullptr, &run);
     if (rc) return rc;
     c ^= 1;
   }
-  return ok();
+  return finish_run(X.ib, s, &run);
 }
 
 // capture what fn enqueues into an executable graph
@@ -347,13 +353,25 @@ int adjoint_impl(btdf_t *h, int64_t n, int64_t K, const double *hist_bar, btdf_g
     const int cur0 = h->cur;
     char *state0 = h->ws + h->off_pop[cur0];
     auto A_of = [&](int64_t t) -> char * { return t == 0 ? state0 : X.store(t - 1); };
+    StepLink link{nullptr, nullptr, 0, 0, 1, 1};
     for (int64_t t = 0; t < n; ++t) {
       LbmParams pt;
       IbParams it;
       X.slot_params(t, X.p, X.ib, &pt, &it);
       void *B = t == n - 1 ? (void *)(h->ws + h->off_pop[1 - cur0]) : (void *)X.store(t);
-      HIPCHK(launch_ib(prec, A_of(t), pt, it, s));
-      HIPCHK(launch_lbm(prec, h->variant, A_of(t), B, pt, TileRange{nullptr, 0, X.nt, 1}, it, s));
+      const TileRange all{nullptr, 0, X.nt, 1};
+      if (one_launch(h, false)) {
+        link.word = (int)(t & 1);
+        HIPCHK(launch_step(prec, A_of(t), B, pt, step_work(h, false), it, link, s));
+        link = StepLink{it.Fx, it.Fy, 0, 1, 1, 1};
+      } else {
+        HIPCHK(launch_ib(prec, A_of(t), pt, it, s));
+        HIPCHK(launch_lbm(prec, h->variant, A_of(t), B, pt, all, it, s));
+      }
+    }
+    if (one_launch(h, false)) {
+      link.word = (int)((n - 1) & 1);
+      HIPCHK(launch_step_flush(X.ib, link, s));
     }
     h->cur = 1 - cur0;
     h->steps += n;

@@ -420,6 +420,36 @@ MoveParams make_move(const btdf_t *h) {
   return mp;
 }
 
+// The work lists of one-launch steps: the tiles with markers one per entry,
+// then the others two per entry, over all tiles and over the near tiles. None
+// for launch shapes that have no such step.
+void step_items(btdf_t *h) {
+  h->work.clear();
+  h->n_work[0] = h->n_work[1] = 0;
+  if (!variant_has_step(h->variant) || h->owner || h->ntx > 0xffff || h->nty > 0x7fff) return;
+  for (int near = 0; near < 2; ++near) {
+    const size_t start = h->work.size();
+    const int first = near ? (int)h->fmap.size() - h->n_near : 0, n = near ? h->n_near : h->ntx * h->nty;
+    auto tile = [&](int k) { return near ? h->fmap[first + k] : k; };
+    auto code = [&](int t) { return t % h->ntx | (t / h->ntx) << 16; };
+    for (int k = 0; k < n; ++k) {
+      const int t = tile(k), m0 = h->tile_off[t], m1 = h->tile_off[t + 1];
+      if (m1 > m0) h->work.push_back({code(t), -1, m0, m1});
+    }
+    bool half = false;
+    for (int k = 0; k < n; ++k) {
+      const int t = tile(k);
+      if (h->tile_off[t + 1] > h->tile_off[t]) continue;
+      if (half)
+        h->work.back().t1 = code(t);
+      else
+        h->work.push_back({code(t), -1, 0, 0});
+      half = !half;
+    }
+    h->n_work[near] = (int)(h->work.size() - start);
+  }
+}
+
 void compute_layout(btdf_t *h) {
   const size_t elt = (size_t)h->prec;
   const int a = h->row_align > 0 ? std::max(1, h->row_align / (int)elt) : 1;
@@ -457,6 +487,8 @@ void compute_layout(btdf_t *h) {
   o = align256(o + (size_t)h->hist_cap * std::max(nb, 1) * 3 * sizeof(double));
   h->off_mk = o;  // X Y U V sdrs Fx Fy rho ux uy
   o = align256(o + 10 * (size_t)std::max(nm, 1) * sizeof(double));
+  h->off_mkalt = o;  // Fx Fy of every other one-launch step
+  o = align256(o + 2 * (size_t)std::max(nm, 1) * sizeof(double));
   h->off_mkw = o;  // 10 values per marker in the population type
   o = align256(o + 10 * (size_t)std::max(nm, 1) * elt);
   h->off_mkixy = o;
@@ -514,6 +546,9 @@ void compute_layout(btdf_t *h) {
   o = align256(o + 2 * (size_t)max_tiles * sizeof(unsigned));
   h->off_near = o;  // one flag per tile
   o = align256(o + (size_t)max_tiles);
+  h->off_work = o;  // one-launch steps: over all tiles and over the near tiles
+  step_items(h);
+  o = align256(o + (h->owner ? 0 : 2 * (size_t)max_tiles * sizeof(StepItem)));
   h->off_pop3 = o;  // the near tiles' intermediate states n+1 .. n+depth-1
   o = align256(o + (h->depth >= 2 || h->reserve_pass ? pop_bytes : 0));
   h->off_pop4 = o;
@@ -594,6 +629,7 @@ IbParams make_ib(const btdf_t *h) {
   ib.ux_l = mk + 8 * M;
   ib.uy_l = mk + 9 * M;
   ib.sdrs = mk + 4 * M;
+  ib.F_alt = h->at<double>(h->off_mkalt);
   ib.mk_w = h->ws + h->off_mkw;
   ib.mk_ixy = h->at<int>(h->off_mkixy);
   ib.cx = bd;
@@ -670,6 +706,7 @@ int upload_bodies(btdf_t *h) {
   put(h->off_fmap, h->fmap.data(), h->fmap.size() * sizeof(int));
   put(h->off_rwin, h->rwin.data(), h->rwin.size() * sizeof(unsigned));
   put(h->off_near, h->near.data(), h->near.size());
+  put(h->off_work, h->work.data(), h->work.size() * sizeof(StepItem));
   put(h->off_moff, h->minv_off.data(), h->minv_off.size() * sizeof(long long));
   put(h->off_minv, h->minv.data(), h->minv.size() * sizeof(double));
   put(h->off_coff, h->cover_off.data(), h->cover_off.size() * sizeof(int));
@@ -763,21 +800,78 @@ int clear_flag(btdf_t *h) {
   return ok();
 }
 
-// One time step on the given buffers: the marker kernel (interpolation,
-// direct force, spread weights), then the lattice kernel over every tile
-// (and the body reductions), then the outlet and rigid motion.
+StepWork step_work(const btdf_t *h, bool near) {
+  return StepWork{h->at<StepItem>(h->off_work) + (near ? h->n_work[0] : 0), h->n_work[near]};
+}
+
+bool one_launch(const btdf_t *h, bool near) {
+  return variant_has_step(h->variant) && h->nm() > 0 && h->nf == 1 && h->method != BTDF_FORCING_IMPLICIT &&
+         h->plane * h->prec < (1LL << 32) && h->n_work[near] > 0 && h->n_work[near] <= kStepMaxWork;
+}
+
+int run_step(btdf_t *h, const LbmParams &p, const IbParams &ib, const void *A, void *B, bool near, hipStream_t s,
+             StepRun *run) {
+  IbParams cur = ib;
+  const int word = (int)((run->left - 1) & 1);  // 0 on the run's last step
+  if (word) {
+    cur.Fx = ib.F_alt;
+    cur.Fy = ib.F_alt + std::max(h->nm(), 1);
+  }
+  StepLink k = run->link;
+  k.word = word;
+  k.reduce = run->pending;
+  k.record = run->left == 1;
+  k.count = 1;
+  HIPCHK(launch_step(h->prec, A, B, p, step_work(h, near), cur, k, s));
+  run->link = StepLink{cur.Fx, cur.Fy, word, 0, 0, 0};
+  run->pending = true;
+  run->left--;
+  return ok();
+}
+
+int finish_run(const IbParams &ib, hipStream_t s, StepRun *run) {
+  if (!run->pending) return ok();
+  HIPCHK(launch_step_flush(ib, run->link, s));
+  run->pending = false;
+  return ok();
+}
+
+// The marker kernel of a step in two launches. A one-launch step before it
+// has its body forces summed first.
+int step_markers(btdf_t *h, const LbmParams &p, const IbParams &ib, const void *A, hipStream_t s, StepRun *run) {
+  const int rc = finish_run(ib, s, run);
+  if (rc) return rc;
+  HIPCHK(launch_ib(h->prec, A, p, ib, s));
+  run->left--;
+  return ok();
+}
+
+// One time step on the given buffers, over every tile: in one launch, or the
+// marker kernel (interpolation, direct force, spread weights) and then the
+// lattice kernel (with the body reductions); then the rigid motion.
 int enqueue_step(btdf_t *h, const LbmParams &p, const IbParams &ib, int src, hipStream_t s,
-                 const StepEvents *te) {
+                 const StepEvents *te, StepRun *run) {
   const void *A = h->ws + h->off_pop[src];
   void *B = h->ws + h->off_pop[1 - src];
+  const bool one = one_launch(h, false);
+  int rc;
   if (te) HIPCHK(hipEventRecord(te->ib0, s));
-  HIPCHK(launch_ib(h->prec, A, p, ib, s));
+  if (!one && (rc = step_markers(h, p, ib, A, s, run))) return rc;
   if (te) HIPCHK(hipEventRecord(te->ib1, s));
-  HIPCHK(launch_lbm(h->prec, h->variant, A, B, p, TileRange{nullptr, 0, h->ntx * h->nty, 1}, ib, s));
+  if (one) {
+    if ((rc = run_step(h, p, ib, A, B, false, s, run))) return rc;
+  } else {
+    HIPCHK(launch_lbm(h->prec, h->variant, A, B, p, TileRange{nullptr, 0, h->ntx * h->nty, 1}, ib, s));
+  }
   if (te) HIPCHK(hipEventRecord(te->a1, s));
-  // moving bodies advance after the step that used their positions (the body
-  // reduction in the lattice launch reads the centres)
-  if (h->any_moving()) HIPCHK(launch_rigid_move(make_move(h), s));
+  // moving bodies advance after the step that used their positions, and after
+  // their forces are summed (with the centres the step used)
+  if (h->any_moving()) {
+    MoveParams mp = make_move(h);
+    mp.reduce = run->pending;
+    HIPCHK(launch_rigid_move(mp, ib, run->link, s));
+    run->pending = false;
+  }
   return ok();
 }
 
@@ -787,7 +881,9 @@ int build_graph(btdf_t *h, const LbmParams &p, const IbParams &ib) {
   hipGraph_t g = nullptr;
   HIPCHK(hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal));
   int rc = 0;
-  for (int k = 0; k < h->graph_chunk && rc == 0; ++k) rc = enqueue_step(h, p, ib, k & 1, h->cap_stream, nullptr);
+  StepRun run{h->graph_chunk};
+  for (int k = 0; k < h->graph_chunk && rc == 0; ++k) rc = enqueue_step(h, p, ib, k & 1, h->cap_stream, nullptr, &run);
+  if (rc == 0) rc = finish_run(ib, h->cap_stream, &run);
   hipError_t e = hipStreamEndCapture(h->cap_stream, &g);
   h->graph_depth = 1;
   if (rc) {
@@ -1122,11 +1218,23 @@ int btdf_set_marker_velocity(btdf_t *h, int body, const double *uv) {
   });
 }
 
-static int enqueue_pass(btdf_t *h, const LbmParams &p, const IbParams &ib, hipStream_t s, hipEvent_t *ev);
+static int enqueue_pass(btdf_t *h, const LbmParams &p, const IbParams &ib, hipStream_t s, hipEvent_t *ev, StepRun *run);
 static int run_blocked(btdf_t *h, const LbmParams &p, const IbParams &ib, int64_t n);
 static bool blocking_active(const btdf_t *h);
 static bool remainder_pair(const btdf_t *h);
 static bool remainder_triple(const btdf_t *h);
+
+// n single steps from the current buffer, a run of their own
+static int single_steps(btdf_t *h, const LbmParams &p, const IbParams &ib, int64_t n) {
+  StepRun run{n};
+  for (; n > 0; --n) {
+    const int rc = enqueue_step(h, p, ib, h->cur, h->stream, nullptr, &run);
+    if (rc) return rc;
+    h->cur ^= 1;
+    h->steps++;
+  }
+  return finish_run(ib, h->stream, &run);
+}
 
 // n steps from the current buffer: graphs of graph_chunk steps where they fit
 static int run_steps(btdf_t *h, const LbmParams &p, const IbParams &ib, int64_t n) {
@@ -1134,9 +1242,7 @@ static int run_steps(btdf_t *h, const LbmParams &p, const IbParams &ib, int64_t 
   int64_t left = n;
   if (h->graph_chunk > 0 && left >= h->graph_chunk + (h->cur ? 1 : 0)) {
     if (h->cur) {  // graphs start from buffer 0
-      if ((rc = enqueue_step(h, p, ib, h->cur, h->stream, nullptr))) return rc;
-      h->cur ^= 1;
-      h->steps++;
+      if ((rc = single_steps(h, p, ib, 1))) return rc;
       left--;
     }
     if ((!h->graph || h->graph_depth != 1) && (rc = build_graph(h, p, ib))) return rc;
@@ -1149,12 +1255,7 @@ static int run_steps(btdf_t *h, const LbmParams &p, const IbParams &ib, int64_t 
       if (h->cur) break;
     }
   }
-  for (; left > 0; --left) {
-    if ((rc = enqueue_step(h, p, ib, h->cur, h->stream, nullptr))) return rc;
-    h->cur ^= 1;
-    h->steps++;
-  }
-  return ok();
+  return single_steps(h, p, ib, left);
 }
 
 // Moving bodies: place the host markers at the mirrored motion, check that
@@ -1192,6 +1293,8 @@ static int rebin(btdf_t *h) {
   int rc;
   if ((rc = upload(h, h->off_toff, h->tile_off.data(), h->tile_off.size() * sizeof(int)))) return rc;
   if ((rc = upload(h, h->off_tlist, h->tile_list.data(), h->tile_list.size() * sizeof(int)))) return rc;
+  step_items(h);
+  if ((rc = upload(h, h->off_work, h->work.data(), h->work.size() * sizeof(StepItem)))) return rc;
   if ((rc = upload(h, h->off_tmap, h->tile_map.data(), h->tile_map.size() * sizeof(int)))) return rc;
   HIPCHK(hipStreamSynchronize(h->stream));
   const double v = max_marker_speed(h);
@@ -1251,24 +1354,40 @@ static hipError_t launch_two_step(const btdf_t *h, const void *A, void *B, void 
   return e;
 }
 
-static int enqueue_pair(btdf_t *h, const LbmParams &p, const IbParams &ib, hipStream_t s, hipEvent_t *ev) {
+// A near tiles' step A -> B in a pass: the marker kernel and the lattice
+// kernel over the near tiles, or both in one launch (then near_markers has
+// nothing to do).
+static int near_markers(btdf_t *h, const LbmParams &p, const IbParams &ib, const void *A, hipStream_t s,
+                        StepRun *run) {
+  return one_launch(h, true) ? ok() : step_markers(h, p, ib, A, s, run);
+}
+static int near_step(btdf_t *h, const LbmParams &p, const IbParams &ib, const void *A, void *B, hipStream_t s,
+                     StepRun *run) {
+  if (one_launch(h, true)) return run_step(h, p, ib, A, B, true, s, run);
+  const TileRange r{h->at<int>(h->off_fmap), h->n_groups(), h->n_near, 1};
+  HIPCHK(launch_lbm(h->prec, h->variant, A, B, p, r, ib, s));
+  return ok();
+}
+
+static int enqueue_pair(btdf_t *h, const LbmParams &p, const IbParams &ib, hipStream_t s, hipEvent_t *ev,
+                        StepRun *run) {
   const void *A = h->ws + h->off_pop[h->cur];
   void *B = h->ws + h->off_pop[1 - h->cur];
   void *X = h->ws + h->off_pop3;
   const int *fm = h->at<int>(h->off_fmap);
   const unsigned char *near = h->at<unsigned char>(h->off_near);
+  int rc;
   if (ev && ev[0]) HIPCHK(hipEventRecord(ev[0], s));
-  HIPCHK(launch_ib(h->prec, A, p, ib, s));
+  if ((rc = near_markers(h, p, ib, A, s, run))) return rc;
   if (ev && ev[1]) HIPCHK(hipEventRecord(ev[1], s));
   if (ev && ev[5]) HIPCHK(hipEventRecord(ev[5], s));
   HIPCHK(launch_two_step(h, A, B, X, near, p, fm, s));
   if (ev && ev[6]) HIPCHK(hipEventRecord(ev[6], s));
-  const int nb0 = h->n_groups();  // the near tiles start here in the map
-  HIPCHK(launch_lbm(h->prec, h->variant, A, X, p, TileRange{fm, nb0, h->n_near, 1}, ib, s));
+  if ((rc = near_step(h, p, ib, A, X, s, run))) return rc;
   if (ev && ev[2]) HIPCHK(hipEventRecord(ev[2], s));
-  HIPCHK(launch_ib(h->prec, X, p, ib, s));
+  if ((rc = near_markers(h, p, ib, X, s, run))) return rc;
   if (ev && ev[3]) HIPCHK(hipEventRecord(ev[3], s));
-  HIPCHK(launch_lbm(h->prec, h->variant, X, B, p, TileRange{fm, nb0, h->n_near, 1}, ib, s));
+  if ((rc = near_step(h, p, ib, X, B, s, run))) return rc;
   if (ev && ev[4]) HIPCHK(hipEventRecord(ev[4], s));
   h->cur ^= 1;
   h->steps += 2;
@@ -1294,18 +1413,19 @@ static int fork_side(btdf_t *h, hipStream_t s) {
 // (which border near tiles) read for their halos, and these go first.
 // ev: 9 events or null: marker kernel E0-E1, near step E1-E2, pass E5-E6,
 // marker kernel E6-E3, near step E3-E4, marker kernel E4-E7, near step E7-E8.
-static int enqueue_triple(btdf_t *h, const LbmParams &p, const IbParams &ib, hipStream_t s, hipEvent_t *ev) {
+static int enqueue_triple(btdf_t *h, const LbmParams &p, const IbParams &ib, hipStream_t s, hipEvent_t *ev,
+                        StepRun *run) {
   const void *A = h->ws + h->off_pop[h->cur];
   void *B = h->ws + h->off_pop[1 - h->cur];
   void *X1 = h->ws + h->off_pop3;
   void *X2 = h->ws + h->off_pop4;
   const int *fm = h->at<int>(h->off_fmap);
   const unsigned char *near = h->at<unsigned char>(h->off_near);
-  const int nb0 = h->n_groups();  // the near tiles start here in the map
+  int rc;
   if (ev && ev[0]) HIPCHK(hipEventRecord(ev[0], s));
-  HIPCHK(launch_ib(h->prec, A, p, ib, s));
+  if ((rc = near_markers(h, p, ib, A, s, run))) return rc;
   if (ev && ev[1]) HIPCHK(hipEventRecord(ev[1], s));
-  HIPCHK(launch_lbm(h->prec, h->variant, A, X1, p, TileRange{fm, nb0, h->n_near, 1}, ib, s));
+  if ((rc = near_step(h, p, ib, A, X1, s, run))) return rc;
   if (ev && ev[2]) HIPCHK(hipEventRecord(ev[2], s));
   // the pass: the smallest groups (which border near tiles) first, the
   // largest last; every launch but the largest interior groups' on a second
@@ -1316,8 +1436,7 @@ static int enqueue_triple(btdf_t *h, const LbmParams &p, const IbParams &ib, hip
   const int n0 = h->n_grp[0] - h->n_edge[0];
   hipStream_t ss = s;
   if (small && n0 > 0) {
-    const int rc = fork_side(h, s);
-    if (rc) return rc;
+    if ((rc = fork_side(h, s))) return rc;
     ss = h->side;
   }
   for (int g = kLevels - 1; g >= 0; --g) {
@@ -1330,13 +1449,13 @@ static int enqueue_triple(btdf_t *h, const LbmParams &p, const IbParams &ib, hip
     HIPCHK(launch_lbm3(h->prec, h->variant, h->gkind[0], A, B, p, fm + h->n_edge[0], n0, X1, X2, near, s));
   if (ss != s) HIPCHK(hipStreamWaitEvent(s, h->join_ev, 0));
   if (ev && ev[6]) HIPCHK(hipEventRecord(ev[6], s));
-  HIPCHK(launch_ib(h->prec, X1, p, ib, s));
+  if ((rc = near_markers(h, p, ib, X1, s, run))) return rc;
   if (ev && ev[3]) HIPCHK(hipEventRecord(ev[3], s));
-  HIPCHK(launch_lbm(h->prec, h->variant, X1, X2, p, TileRange{fm, nb0, h->n_near, 1}, ib, s));
+  if ((rc = near_step(h, p, ib, X1, X2, s, run))) return rc;
   if (ev && ev[4]) HIPCHK(hipEventRecord(ev[4], s));
-  HIPCHK(launch_ib(h->prec, X2, p, ib, s));
+  if ((rc = near_markers(h, p, ib, X2, s, run))) return rc;
   if (ev && ev[7]) HIPCHK(hipEventRecord(ev[7], s));
-  HIPCHK(launch_lbm(h->prec, h->variant, X2, B, p, TileRange{fm, nb0, h->n_near, 1}, ib, s));
+  if ((rc = near_step(h, p, ib, X2, B, s, run))) return rc;
   if (ev && ev[8]) HIPCHK(hipEventRecord(ev[8], s));
   h->cur ^= 1;
   h->steps += 3;
@@ -1348,7 +1467,8 @@ static int enqueue_triple(btdf_t *h, const LbmParams &p, const IbParams &ib, hip
 // each of their steps. ev: 2d + 2 events or null: marker kernel E0-E1, near
 // step E1-E2, pass E2-E3, then for each later step s = 1 .. d-1 the marker
 // kernel E(2s+1)-E(2s+2) and the near step E(2s+2)-E(2s+3).
-static int enqueue_deep(btdf_t *h, const LbmParams &p, const IbParams &ib, hipStream_t s, hipEvent_t *ev) {
+static int enqueue_deep(btdf_t *h, const LbmParams &p, const IbParams &ib, hipStream_t s, hipEvent_t *ev,
+                        StepRun *run) {
   const int d = h->depth;
   const void *A = h->ws + h->off_pop[h->cur];
   void *B = h->ws + h->off_pop[1 - h->cur];
@@ -1356,12 +1476,12 @@ static int enqueue_deep(btdf_t *h, const LbmParams &p, const IbParams &ib, hipSt
   void *X[5] = {nullptr, h->ws + h->off_pop3, h->ws + h->off_pop4, h->ws + h->off_pop5, h->ws + h->off_pop6};
   const int *fm = h->at<int>(h->off_fmap);
   const unsigned *rwin = h->at<unsigned>(h->off_rwin);
-  const int nb0 = h->n_groups();  // the near tiles start here in the map
+  int rc;
   auto mark = [&](int k) -> hipError_t { return ev && ev[k] ? hipEventRecord(ev[k], s) : hipSuccess; };
   HIPCHK(mark(0));
-  HIPCHK(launch_ib(h->prec, A, p, ib, s));
+  if ((rc = near_markers(h, p, ib, A, s, run))) return rc;
   HIPCHK(mark(1));
-  HIPCHK(launch_lbm(h->prec, h->variant, A, X[1], p, TileRange{fm, nb0, h->n_near, 1}, ib, s));
+  if ((rc = near_step(h, p, ib, A, X[1], s, run))) return rc;
   HIPCHK(mark(2));
   // the pass: the smaller groups' launches on a second stream, beside the
   // largest groups' launch (they are one to three waves of workgroups long,
@@ -1369,7 +1489,6 @@ static int enqueue_deep(btdf_t *h, const LbmParams &p, const IbParams &ib, hipSt
   bool small = false;
   for (int g = 1; g < kLevels; ++g) small = small || h->n_grp[g] > 0;
   if (small && h->n_grp[0]) {
-    int rc;
     if ((rc = fork_side(h, s))) return rc;
     for (int g = kLevels - 1; g >= 1; --g)
       if (h->n_grp[g])
@@ -1388,9 +1507,9 @@ static int enqueue_deep(btdf_t *h, const LbmParams &p, const IbParams &ib, hipSt
   HIPCHK(mark(3));
   for (int k = 1; k < d; ++k) {
     void *dst = k + 1 < d ? X[k + 1] : B;
-    HIPCHK(launch_ib(h->prec, X[k], p, ib, s));
+    if ((rc = near_markers(h, p, ib, X[k], s, run))) return rc;
     HIPCHK(mark(2 * k + 2));
-    HIPCHK(launch_lbm(h->prec, h->variant, X[k], dst, p, TileRange{fm, nb0, h->n_near, 1}, ib, s));
+    if ((rc = near_step(h, p, ib, X[k], dst, s, run))) return rc;
       HIPCHK(mark(2 * k + 3));
   }
   h->cur ^= 1;
@@ -1398,9 +1517,10 @@ static int enqueue_deep(btdf_t *h, const LbmParams &p, const IbParams &ib, hipSt
   return ok();
 }
 
-static int enqueue_pass(btdf_t *h, const LbmParams &p, const IbParams &ib, hipStream_t s, hipEvent_t *ev) {
-  if (h->depth >= 4) return enqueue_deep(h, p, ib, s, ev);
-  return h->depth == 3 ? enqueue_triple(h, p, ib, s, ev) : enqueue_pair(h, p, ib, s, ev);
+static int enqueue_pass(btdf_t *h, const LbmParams &p, const IbParams &ib, hipStream_t s, hipEvent_t *ev,
+                        StepRun *run) {
+  if (h->depth >= 4) return enqueue_deep(h, p, ib, s, ev, run);
+  return h->depth == 3 ? enqueue_triple(h, p, ib, s, ev, run) : enqueue_pair(h, p, ib, s, ev, run);
 }
 
 // a graph of graph_chunk / depth whole passes, starting from buffer 0
@@ -1413,7 +1533,9 @@ static int build_pass_graph(btdf_t *h, const LbmParams &p, const IbParams &ib, i
   hipGraph_t g = nullptr;
   HIPCHK(hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal));
   int rc = 0;
-  for (int k = 0; k < passes && rc == 0; ++k) rc = enqueue_pass(h, p, ib, h->cap_stream, nullptr);
+  StepRun run{(int64_t)passes * h->depth};
+  for (int k = 0; k < passes && rc == 0; ++k) rc = enqueue_pass(h, p, ib, h->cap_stream, nullptr, &run);
+  if (rc == 0) rc = finish_run(ib, h->cap_stream, &run);
   hipError_t e = hipStreamEndCapture(h->cap_stream, &g);
   h->cur = cur;  // capturing ran nothing
   h->steps = steps;
@@ -1441,9 +1563,7 @@ static int run_blocked(btdf_t *h, const LbmParams &p, const IbParams &ib, int64_
   int rc;
   if (per > 0 && left >= (int64_t)per * d + (h->cur ? 1 : 0)) {
     if (h->cur) {  // graphs start from buffer 0
-      if ((rc = enqueue_step(h, p, ib, h->cur, h->stream, nullptr))) return rc;
-      h->cur ^= 1;
-      h->steps++;
+      if ((rc = single_steps(h, p, ib, 1))) return rc;
       left--;
     }
     if ((!h->graph || h->graph_depth != d) && (rc = build_pass_graph(h, p, ib, per))) return rc;
@@ -1455,22 +1575,23 @@ static int run_blocked(btdf_t *h, const LbmParams &p, const IbParams &ib, int64_
       if (h->cur) break;
     }
   }
+  StepRun run{left};
   for (; left >= d; left -= d)
-    if ((rc = enqueue_pass(h, p, ib, h->stream, nullptr))) return rc;
+    if ((rc = enqueue_pass(h, p, ib, h->stream, nullptr, &run))) return rc;
   if (left >= 3 && remainder_triple(h)) {
-    if ((rc = enqueue_triple(h, p, ib, h->stream, nullptr))) return rc;
+    if ((rc = enqueue_triple(h, p, ib, h->stream, nullptr, &run))) return rc;
     left -= 3;
   }
   if (left == 2 && remainder_pair(h)) {
-    if ((rc = enqueue_pair(h, p, ib, h->stream, nullptr))) return rc;
+    if ((rc = enqueue_pair(h, p, ib, h->stream, nullptr, &run))) return rc;
     left = 0;
   }
   for (; left > 0; --left) {
-    if ((rc = enqueue_step(h, p, ib, h->cur, h->stream, nullptr))) return rc;
+    if ((rc = enqueue_step(h, p, ib, h->cur, h->stream, nullptr, &run))) return rc;
     h->cur ^= 1;
     h->steps++;
   }
-  return ok();
+  return finish_run(ib, h->stream, &run);
 }
 
 static bool blocking_active(const btdf_t *h) {
@@ -1531,6 +1652,7 @@ static int timed_impl(btdf_t *h, int64_t n, double *out, bool pass_only = false)
       if ((int)(i % NE) != pa && (int)(i % NE) != pb) ev[i] = nullptr;
   double tib = 0.0, tlbm = 0.0, tpair = 0.0;
   int64_t done = 0, pass_steps = 0;
+  StepRun run{n};
   rc = ok();
   while (done < n && rc == 0) {
     // entries of this round: passes of d steps while d are left; three
@@ -1546,20 +1668,20 @@ static int timed_impl(btdf_t *h, int64_t n, double *out, bool pass_only = false)
     const bool moving = h->any_moving();
     for (int k = 0; k < m && rc == 0; ++k) {
       if (rem3) {
-        rc = enqueue_triple(h, p, ib, h->stream, pass_only ? nullptr : &ev[NE * k]);
+        rc = enqueue_triple(h, p, ib, h->stream, pass_only ? nullptr : &ev[NE * k], &run);
         continue;
       }
       if (rem2) {
-        rc = enqueue_pair(h, p, ib, h->stream, pass_only ? nullptr : &ev[NE * k]);
+        rc = enqueue_pair(h, p, ib, h->stream, pass_only ? nullptr : &ev[NE * k], &run);
         continue;
       }
       if (pairs) {
-        rc = enqueue_pass(h, p, ib, h->stream, &ev[NE * k]);
+        rc = enqueue_pass(h, p, ib, h->stream, &ev[NE * k], &run);
         continue;
       }
       if (moving && h->steps_to_rebin <= 0 && (rc = rebin(h))) break;
       const StepEvents te{ev[NE * k], ev[NE * k + 1], ev[NE * k + 2], ev[NE * k + 3], ev[NE * k + 4], ev[NE * k + 5]};
-      rc = enqueue_step(h, p, ib, h->cur, h->stream, pass_only ? nullptr : &te);
+      rc = enqueue_step(h, p, ib, h->cur, h->stream, pass_only ? nullptr : &te, &run);
       h->cur ^= 1;
       h->steps++;
       if (moving) {
@@ -1626,7 +1748,8 @@ static int timed_impl(btdf_t *h, int64_t n, double *out, bool pass_only = false)
     }
     done += (int64_t)dk * m;
   }
-  if (rc) return rc;
+  if (rc || (rc = finish_run(ib, h->stream, &run))) return rc;
+  HIPCHK(hipStreamSynchronize(h->stream));
   h->stepped = true;
   out[0] = h->nb() ? tib / (double)n : 0.0;
   out[1] = tlbm / (double)n;

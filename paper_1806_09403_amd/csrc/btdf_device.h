@@ -243,6 +243,28 @@ struct TileRange {
   int count_step;  // this launch advances the device step counter
 };
 
+// How one launch of the one-launch step (btdf_step.hip) follows the step
+// before it: that step's body forces are summed by this launch, from the
+// marker forces it left (two buffers in turn) and the ring entry its counter
+// workgroup wrote (slot words 0 and 1 in turn).
+struct StepLink {
+  const double *Fx, *Fy;  // the previous step's marker forces
+  int word;               // the slot word of this step; the previous step's is the other
+  int reduce;             // 1: sum the previous step's forces
+  int record;             // 1: leave this step's marker values
+  int count;              // 1: advance the step counter
+};
+// What one workgroup of the one-launch step does: a tile with the markers
+// m0 .. m1 of the tile list, or two tiles without markers (t1 = -1: one).
+// Tiles as tile column | tile row << 16.
+struct alignas(16) StepItem {
+  int t0, t1, m0, m1;
+};
+struct StepWork {
+  const StepItem *items;
+  int count;
+};
+
 // rigid body motion, one workgroup per body after each step
 struct MoveParams {
   int nb;
@@ -252,6 +274,7 @@ struct MoveParams {
   double *cx, *cy;     // body centres
   double *X, *Y, *U, *V;
   const double *rxy;   // [nm][2]: offset from the centre at angle 0
+  int reduce;          // 1: sum the step's body forces first (one-launch steps)
 };
 
 struct IbParams {
@@ -262,6 +285,7 @@ struct IbParams {
   const double *cx, *cy;
   const double *body_sdrs;  // drs * ds per body
   const double *sdrs;       // drs * ds per marker
+  double *F_alt;            // [2][nm]: the marker forces' second buffer (one-launch steps)
   double *Fx, *Fy, *rho_l, *ux_l, *uy_l;
   void *mk_w;               // spread weights and scaled forces for the lattice kernel
   int *mk_ixy;
@@ -568,6 +592,42 @@ __device__ __forceinline__ T pull(const T *__restrict__ A, const LbmParams &p, i
   }
   if (p.xper) sx = sx < 0 ? sx + p.nx : (sx >= p.nx ? sx - p.nx : sx);
   return load<T, NTL>(&A[(long long)q * p.plane + (long long)sy * p.pitch + sx]);
+}
+
+// All nine pulls of a node, with the boundary readings of pull(): the three
+// columns and rows are wrapped (or, at a wall, held at the node's own row)
+// once for all directions, and a node next to a wall then replaces the three
+// populations that came from beyond it.
+template <typename T, bool NTL = false>
+__device__ __forceinline__ void pull9(const T *__restrict__ A, const LbmParams &p, int x, int y, T (&g)[9]) {
+#pragma clang fp contract(off)
+  int xm = x - 1, xp = x + 1, ym = y - 1, yp = y + 1;
+  if (p.xper) {
+    xm = xm < 0 ? xm + p.nx : xm;
+    xp = xp >= p.nx ? xp - p.nx : xp;
+  }
+  if (p.yper) {
+    ym = ym < 0 ? ym + p.ny : ym;
+    yp = yp >= p.ny ? yp - p.ny : yp;
+  } else {
+    ym = ym < 0 ? 0 : ym;
+    yp = yp >= p.ny ? p.ny - 1 : yp;
+  }
+  const T *row[3] = {A + (long long)ym * p.pitch, A + (long long)y * p.pitch, A + (long long)yp * p.pitch};
+  const int col[3] = {xm, x, xp};
+#pragma unroll
+  for (int q = 0; q < 9; ++q) g[q] = load<T, NTL>(row[1 - ey(q)] + (long long)q * p.plane + col[1 - ex(q)]);
+  if (!p.yper && (y == 0 || y == p.ny - 1)) {
+    const __attribute__((address_space(4))) T *k = (const __attribute__((address_space(4))) T *)konst<T>(p);
+#pragma unroll
+    for (int q = 2; q < 9; ++q) {
+      if (ey(q) == 0 || y != (ey(q) > 0 ? 0 : p.ny - 1)) continue;
+      if (p.slip)
+        g[q] = load<T, NTL>(row[1] + (long long)mir_y(q) * p.plane + col[1 - ex(q)]) + k[27 + q];
+      else
+        g[q] = load<T, NTL>(row[1] + (long long)opp(q) * p.plane + x) + k[18 + q];
+    }
+  }
 }
 
 // The periodic image of a node index in [0, n): ((i mod n) + n) mod n,

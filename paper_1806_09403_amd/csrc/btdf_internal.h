@@ -101,6 +101,10 @@ struct btdf_sim {
   int n_ring[btdf::kLevels] = {};  // passes of four or five steps: groups bordering a near tile (listed first)
   long long pass_nodes = 0;        // grid nodes in the blocked pass (partial tiles counted by their nodes)
   int n_near = 0;
+  // one-launch steps: what each workgroup does, over all tiles, then over the
+  // pass's near tiles
+  std::vector<btdf::StepItem> work;
+  int n_work[2] = {0, 0};
   int n_groups() const {
     int k = 0;
     for (int i = 0; i < btdf::kLevels; ++i) k += n_grp[i];
@@ -124,9 +128,9 @@ struct btdf_sim {
   int pitch = 0;
   long long plane = 0;
   size_t off_pop[2] = {0, 0}, off_ctl = 0, grid_bytes = 0;
-  size_t off_hist = 0, off_mk = 0, off_mkw = 0, off_mkixy = 0, off_mkbody = 0, off_body = 0, off_boff = 0,
+  size_t off_hist = 0, off_mk = 0, off_mkalt = 0, off_mkw = 0, off_mkixy = 0, off_mkbody = 0, off_body = 0, off_boff = 0,
          off_toff = 0, off_tlist = 0, off_tmap = 0, off_coff = 0, off_clist = 0, off_mdfc = 0, off_mdff = 0,
-         off_moff = 0, off_minv = 0, off_motion = 0, off_rxy = 0, off_fmap = 0, off_rwin = 0, off_near = 0, off_pop3 = 0, off_pop4 = 0, off_pop5 = 0, off_pop6 = 0, total = 0;
+         off_moff = 0, off_minv = 0, off_motion = 0, off_rxy = 0, off_fmap = 0, off_rwin = 0, off_near = 0, off_work = 0, off_pop3 = 0, off_pop4 = 0, off_pop5 = 0, off_pop6 = 0, total = 0;
   bool layout_ok = false;  // host layout current for bodies and tiles
   bool device_ok = false;  // body part uploaded into the workspace
   bool state_ok = false;   // populations hold a state
@@ -210,6 +214,8 @@ constexpr long long kBlockMinNodes = 1ll << 20;
 constexpr int kDefaultDepth = 5;
 // width in tile columns of the bands down which groups two tiles tall are launched
 constexpr int kSquareBand = 32;
+// most workgroups of a one-launch step
+constexpr int kStepMaxWork = 2048;
 std::string forcing_setup(btdf_t *h);
 LbmParams make_params(const btdf_t *h);
 IbParams make_ib(const btdf_t *h);
@@ -224,9 +230,26 @@ int destroy_impl(btdf_t *h);
 struct StepEvents {
   hipEvent_t ib0, ib1, a0, a1, b0, b1;
 };
+// A run of consecutive steps enqueued on one stream. One-launch steps
+// (btdf_step.hip) leave their body forces to the next step's launch, so a run
+// ends with finish_run; the marker forces alternate between two buffers so
+// that the last step's are in the handle's own.
+struct StepRun {
+  int64_t left = 0;        // steps still to enqueue
+  bool pending = false;    // the last one's body forces are not summed yet
+  StepLink link{};
+};
+// Whether a step takes one launch, over all tiles or (near) over the blocked
+// pass's near tiles.
+bool one_launch(const btdf_t *h, bool near);
+// a one-launch step A -> B
+int run_step(btdf_t *h, const LbmParams &p, const IbParams &ib, const void *A, void *B, bool near, hipStream_t s,
+             StepRun *run);
+StepWork step_work(const btdf_t *h, bool near);
+int finish_run(const IbParams &ib, hipStream_t s, StepRun *run);
 // one step from population buffer src into the other, on stream s
 int enqueue_step(btdf_t *h, const LbmParams &p, const IbParams &ib, int src, hipStream_t s,
-                 const StepEvents *te);
+                 const StepEvents *te, StepRun *run);
 
 }  // namespace host
 }  // namespace btdf

@@ -11,7 +11,13 @@ void variant_tile(int v, int *tx, int *ty);
 hipError_t launch_lbm(int prec, int variant, const void *A, void *B, const LbmParams &p, const TileRange &r,
                       const IbParams &ib, hipStream_t s);
 hipError_t launch_ib(int prec, const void *A, const LbmParams &p, const IbParams &ib, hipStream_t s);
-hipError_t launch_rigid_move(const MoveParams &mp, hipStream_t s);
+// a whole step A -> B over the tiles of w in one launch (direct forcing, one
+// pass), and the body forces of the step k names (btdf_step.hip)
+bool variant_has_step(int variant);
+hipError_t launch_step(int prec, const void *A, void *B, const LbmParams &p, const StepWork &w, const IbParams &ib,
+                       const StepLink &k, hipStream_t s);
+hipError_t launch_step_flush(const IbParams &ib, const StepLink &k, hipStream_t s);
+hipError_t launch_rigid_move(const MoveParams &mp, const IbParams &ib, const StepLink &k, hipStream_t s);
 // two steps A -> C over the listed groups of width lattice tiles; with near
 // non-null, edge nodes next to a near tile also store their first step in X
 hipError_t launch_lbm2(int prec, int variant, int width, const void *A, void *C, const LbmParams &p, const int *map,

@@ -1,0 +1,303 @@
+// btdf_tile.h -- one tile of the lattice in one time step (device code of the
+// single-step lattice kernels in btdf_kernels.hip and of the one-launch step
+// in btdf_step.hip): the streaming pull, the spread gather of the tile's
+// markers, the collision and the channel's ghost columns; and the per-body
+// sums of eq 27.
+#pragma once
+
+#include "btdf_device.h"
+
+namespace btdf {
+
+// Hydrodynamic force and torque on body b (eq 27 with the body's sign): a
+// workgroup of NT lanes sums its markers' forces (Fl_x, Fl_y) in a fixed
+// order and writes them to the step's entry (slot) of the history ring.
+template <int NT>
+__device__ void body_reduce(const IbParams &ib, const double *Fl_x, const double *Fl_y, int slot, int b, int tid,
+                            double (*red)[NT / 64]) {
+  const int l0 = ib.body_off[b], l1 = ib.body_off[b + 1];
+  const double cx = ib.cx[b], cy = ib.cy[b];
+  double sfx = 0.0, sfy = 0.0, stz = 0.0;
+  const bool per_marker = ib.method == 2;  // RKPM spreads with a factor per marker
+  for (int l = l0 + tid; l < l1; l += NT) {
+    const double Fx = Fl_x[l], Fy = Fl_y[l];
+    if (per_marker) {
+      const double w = ib.sdrs[l];
+      sfx += w * Fx;
+      sfy += w * Fy;
+      stz += w * ((ib.X[l] - cx) * Fy - (ib.Y[l] - cy) * Fx);
+    } else {
+      sfx += Fx;
+      sfy += Fy;
+      stz += (ib.X[l] - cx) * Fy - (ib.Y[l] - cy) * Fx;
+    }
+  }
+  sfx = wave_sum(sfx);
+  sfy = wave_sum(sfy);
+  stz = wave_sum(stz);
+  const int lane = tid & 63, w = tid >> 6;
+  if (lane == 0) {
+    red[0][w] = sfx;
+    red[1][w] = sfy;
+    red[2][w] = stz;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0;
+    for (int k = 0; k < NT / 64; ++k) {
+      s0 += red[0][k];
+      s1 += red[1][k];
+      s2 += red[2][k];
+    }
+    const double s = per_marker ? 1.0 : ib.body_sdrs[b];
+    double *h = ib.hist + ((long long)slot * ib.nb + b) * 3;
+    h[0] = -s * s0;
+    h[1] = -s * s1;
+    h[2] = -s * s2;
+  }
+}
+
+constexpr int kChunk = 64;  // markers staged in LDS per pass
+
+template <typename T, bool NT>
+__device__ __forceinline__ void store(T *ptr, T v) {
+  const global_ptr<T> g = (global_ptr<T>)ptr;  // device memory: a global access
+  if (NT)
+    __builtin_nontemporal_store(v, g);
+  else
+    *g = v;
+}
+
+// A batch case's stop flag (nonzero once the case went unstable), read
+// with an atomic load at the start of a workgroup: the read is in flight with
+// the population loads and is not moved down to its use. Batch kernels pass
+// the case's flag, or kNoStop when unstable cases are not masked, so the load
+// needs no branch around it (whose join would wait for it at once). The
+// address carries a per-lane zero the compiler cannot see through, so the
+// value stays per lane instead of being moved to a scalar register (and
+// waited for) right after the load.
+__device__ const int kNoStop = 0;
+template <bool STOP>
+__device__ __forceinline__ int stop_flag(const int *stop) {
+  if constexpr (STOP) {
+    int zero;
+    asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
+    return __hip_atomic_load((global_ptr<const int>)stop + zero, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  return 0;
+}
+
+// The spread force of the cnt markers staged in LDS (stencil origins, then
+// wx[4], wy[4], drs ds F_x, drs ds F_y) on this thread's nodes (xb + k BX, y),
+// added in ascending marker order. Each lane first tests one marker against
+// the rows of its wave (WR rows from yw); the wave then walks the set bits of
+// that mask, four markers at a time with their LDS reads in flight together,
+// and each lane keeps the sums of the markers whose stencil covers its node.
+// A loop over all markers with a branch per marker instead waited for two
+// dependent LDS reads per marker (200x120 FP64 channel, 50 markers: 13.3 us a
+// step then, 12.4 now; 2000x800 FP32 shedding: 28.6 and 26.2).
+template <typename T, int BX, int NPT, int WR>
+__device__ __forceinline__ void spread_gather(const int (&s_ix)[kChunk], const int (&s_iy)[kChunk],
+                                              const T (&s_w)[kChunk][10], int cnt, int S, const LbmParams &p, int xb,
+                                              int y, int yw, T (&fx)[NPT], T (&fy)[NPT]) {
+  static_assert(kChunk <= 64, "one marker per lane of a wave");
+  const int lane = (int)(threadIdx.y * BX + threadIdx.x) & 63;
+  // rows yw .. yw + WR - 1 meet rows iy .. iy + S - 1 (mod ny) if e < S + WR - 1
+  int e = yw + WR - 1 - s_iy[lane < cnt ? lane : 0];
+  if (p.yper && e < 0) e += p.ny;
+  unsigned long long m = __builtin_amdgcn_ballot_w64(lane < cnt && (unsigned)e < (unsigned)(S + WR - 1));
+  while (m) {
+    int id[4];
+    bool on[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      on[u] = m != 0;
+      id[u] = on[u] ? __builtin_ctzll(m) : id[u ? u - 1 : 0];
+      m &= m - 1;
+    }
+    int dy[4];
+    T wy[4], Fx[4], Fy[4];
+    int ix[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      dy[u] = y - s_iy[id[u]];
+      ix[u] = s_ix[id[u]];
+      Fx[u] = s_w[id[u]][8];
+      Fy[u] = s_w[id[u]][9];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      if (p.yper && dy[u] < 0) dy[u] += p.ny;
+      on[u] = on[u] && (unsigned)dy[u] < (unsigned)S;
+      wy[u] = s_w[id[u]][4 + (dy[u] & 3)];
+    }
+#pragma unroll
+    for (int k = 0; k < NPT; ++k) {
+      int dx[4];
+      T wx[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        dx[u] = xb + k * BX - ix[u];
+        if (p.xper && dx[u] < 0) dx[u] += p.nx;
+        wx[u] = s_w[id[u]][dx[u] & 3];
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const T W = wx[u] * wy[u];
+        const T ax = fmx(W, Fx[u], fx[k]), ay = fmx(W, Fy[u], fy[k]);
+        const bool in = on[u] && (unsigned)dx[u] < (unsigned)S;
+        fx[k] = in ? ax : fx[k];
+        fy[k] = in ? ay : fy[k];
+      }
+    }
+  }
+}
+
+// Convective outlet (d/dt + U d/dx = 0 on the ghost column, implicit upwind):
+// the ghost of B is (ghost of A + U column nx-2 of B) / (1 + U), written by
+// the lane that has just made column nx-2 (base: its offset, out: its
+// values). The reference offsets of the stored deviations cancel (the
+// weights sum to one). Here it costs nothing measurable: as a launch after
+// the step it was one round trip per population on one thread per row, 9.8
+// us at 401 rows and 15.3 us at 1601 (the 1601^2 far-field run: 49.5 us a
+// step then, 33.0 now). The loads stay behind the collision so that the
+// kernel's registers are the collision's.
+template <typename T>
+__device__ __forceinline__ void conv_outlet_node(const T *__restrict__ A, T *__restrict__ B, const LbmParams &p,
+                                                 long long base, const T (&out)[9]) {
+  const T U = (T)p.uconv, den = (T)(1.0 + p.uconv);
+  T g[9];
+  __builtin_amdgcn_sched_barrier(0);  // (no earlier: the loads' registers would add to the collision's)
+#pragma unroll
+  for (int q = 0; q < 9; ++q) g[q] = load<T>(&A[(long long)q * p.plane + base + 1]);
+#pragma unroll
+  for (int q = 0; q < 9; ++q) {
+    B[(long long)q * p.plane + base + 1] = (g[q] + U * out[q]) / den;
+    __builtin_amdgcn_sched_barrier(0);  // one division's temporaries at a time
+  }
+}
+
+// one tile t of the lattice: streaming pull, spread gather, collision; with
+// STOP and *stop set, nothing is stored (a stopped batch case)
+template <typename T, int BX, int BY, int NPT, bool NT, bool NTL, bool STOP = false>
+__device__ __forceinline__ void lbm_tile(const T *__restrict__ A, T *__restrict__ B, const LbmParams &p, int t,
+                                         const int *stop = nullptr) {
+  constexpr int TX = BX * NPT;
+  const int halt = stop_flag<STOP>(stop);
+  __shared__ int s_ix[kChunk], s_iy[kChunk];
+  __shared__ T s_w[kChunk][10];  // wx[4], wy[4], drs ds F_x, drs ds F_y
+  const int tyi = t / p.ntx;
+  const int txi = t - tyi * p.ntx;
+  const int y = tyi * BY + (int)threadIdx.y;
+  const int xb = txi * TX + (int)threadIdx.x;
+
+  // A wave whose nodes and their neighbours need no wrap and no wall takes
+  // the interior path: every pull is one load from a wave-uniform base plus
+  // the lane's byte offset. A wave spans WR rows of the tile (1 if BX >= 64).
+  constexpr int WR = BX >= 64 ? 1 : 64 / BX;
+  constexpr int WX = BX >= 64 ? 64 : BX;
+  const int yw = __builtin_amdgcn_readfirstlane(y - (BX >= 64 ? 0 : ((int)threadIdx.y % WR)));
+  const int xw = __builtin_amdgcn_readfirstlane(BX >= 64 ? txi * TX + ((int)threadIdx.x & ~63) : txi * TX);
+  // (a wave that holds column nx-2 of a channel also writes the outlet ghost)
+  const bool interior = p.interior && yw >= 1 && yw + WR <= p.ny - 1 && xw >= 1 &&
+                        xw + WX + (NPT - 1) * BX <= p.nx - 1 - (p.outlet ? 1 : 0);
+  const unsigned rowoff = (unsigned)(y - yw) * (unsigned)p.pitch;
+
+  // the pulls are issued first, so they are in flight while the tile
+  // gathers its markers' forces
+  T g[NPT][9];
+  bool live[NPT];
+#pragma unroll
+  for (int k = 0; k < NPT; ++k) {
+    const int x = xb + k * BX;
+    live[k] = y < p.ny && (interior || (x >= p.i0 && x <= p.i1));
+    if (!live[k]) continue;
+    // byte offset of the node from the wave's first row: one 32-bit register
+    // shared by all loads and stores of the interior path
+    const unsigned xoff = (rowoff + (unsigned)x) * (unsigned)sizeof(T);
+    if (interior) {
+#pragma unroll
+      for (int q = 0; q < 9; ++q) {
+        const char *base = reinterpret_cast<const char *>(A + (long long)q * p.plane +
+                                                          (long long)(yw - ey(q)) * p.pitch - ex(q));
+        g[k][q] = load<T, NTL>(reinterpret_cast<const T *>(base + xoff));
+      }
+    } else {
+      pull9<T, NTL>(A, p, x, y, g[k]);
+    }
+  }
+
+  T fib_x[NPT], fib_y[NPT];
+#pragma unroll
+  for (int k = 0; k < NPT; ++k) fib_x[k] = fib_y[k] = (T)0;
+
+  // spread (eqs 13, 15) as a gather over the markers listed for this tile;
+  // the marker kernel left each marker's weights and drs ds F_l
+  const int m0 = ldg(p.tile_off, t), m1 = ldg(p.tile_off, t + 1);
+  const bool forced = m1 > m0;
+  if (forced) {
+    const int S = stencil_size(p.kind);
+    const int tid = (int)threadIdx.y * BX + (int)threadIdx.x;
+    const T *mw = reinterpret_cast<const T *>(p.mk_w);
+    for (int c0 = m0; c0 < m1; c0 += kChunk) {
+      const int cnt = min(kChunk, m1 - c0);
+      __syncthreads();
+      if (tid < cnt) {
+        const int l = ldg(p.tile_list, c0 + tid);
+        s_ix[tid] = ldg(p.mk_ixy, 2 * l);
+        s_iy[tid] = ldg(p.mk_ixy, 2 * l + 1);
+#pragma unroll
+        for (int k = 0; k < 10; ++k) s_w[tid][k] = ldg(mw, 10 * (long long)l + k);
+      }
+      __syncthreads();
+      spread_gather<T, BX, NPT, WR>(s_ix, s_iy, s_w, cnt, S, p, xb, y, yw, fib_x, fib_y);
+    }
+  }
+  if (y >= p.ny || halt) return;  // (after the gather's last barrier)
+
+  const CollK<T> &K = coll<T>(p);
+  bool bad = false;
+#pragma unroll
+  for (int k = 0; k < NPT; ++k) {
+    const int x = xb + k * BX;
+    if (!live[k]) continue;
+    const unsigned xoff = (rowoff + (unsigned)x) * (unsigned)sizeof(T);
+    T out[9], rho;
+    if (forced) {
+      const ForceK<T> F = force_terms<T>(K, (T)(p.Gx + (double)fib_x[k]), (T)(p.Gy + (double)fib_y[k]));
+      collide<T>(g[k], F, K, out, rho);
+    } else {
+      collide<T>(g[k], gforce<T>(p), K, out, rho);
+    }
+    bad |= !rho_ok(rho);
+    if (interior) {
+#pragma unroll
+      for (int q = 0; q < 9; ++q) {
+        char *base = reinterpret_cast<char *>(B + (long long)q * p.plane + (long long)yw * p.pitch);
+        store<T, NT>(reinterpret_cast<T *>(base + xoff), out[q]);
+      }
+      continue;
+    }
+    const long long base = (long long)y * p.pitch + x;
+#pragma unroll
+    for (int q = 0; q < 9; ++q) store<T, NT>(&B[(long long)q * p.plane + base], out[q]);
+    if (p.inlet && x == 1) {
+      // inlet ghost: equilibrium at the inflow velocity, density of column 1
+      const T dr = inlet_dr<T>(out);
+      const long long gb = (long long)y * p.pitch;
+#pragma unroll
+      for (int q = 0; q < 9; ++q) B[(long long)q * p.plane + gb] = inlet_ghost<T>(dr, p, q);
+    }
+    if (p.outlet && x == p.nx - 2) {
+      if (p.outlet == 1) {
+#pragma unroll
+        for (int q = 0; q < 9; ++q) B[(long long)q * p.plane + base + 1] = out[q];
+      } else {
+        conv_outlet_node<T>(A, B, p, base, out);
+      }
+    }
+  }
+  if (bad) p.flag[0] = -1;
+}
+
+}  // namespace btdf
