@@ -230,7 +230,7 @@ int forward_steps(const Adj &X, int64_t len, int c, hipStream_t s) {
     if (rc) return rc;
     c ^= 1;
   }
-  return finish_run(X.ib, s, &run);
+  return finish_run(X.h, X.ib, s, &run);
 }
 
 // capture what fn enqueues into an executable graph

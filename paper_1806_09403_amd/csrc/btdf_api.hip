@@ -15,6 +15,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -209,6 +210,28 @@ void group_kinds(int variant, int prec, int d, int kind[kLevels]) {
   for (int i = 0; i < kLevels; ++i) kind[i] = d >= 5 ? squares[i] : rows[i];
 }
 
+// Whether the pass's large groups run on a second stream beside the near
+// tiles' steps: where those are few. They take a chain of small launches that
+// leaves most of the GPU idle, and wait only for the states of the groups that
+// border them; beside the chain the large groups cost little. Measured per
+// step, in turn and beside: 26.2 and 14.3 us on 2000x800 with one cylinder,
+// 36.2 and 32.3 on 2048^2 with 60 of D = 24, 42.8 and 40.2 with 125, equal at
+// 77 on 3072^2 with 280 (3100 tiles with markers; FP32, FP64 alike): with many
+// near tiles both fill the GPU and there is nothing to gain.
+bool pass_beside(const btdf_t *h, const std::vector<char> &near) {
+  int kind[kLevels];
+  group_kinds(h->variant, h->prec, h->depth, kind);
+  if (h->owner || h->edge_tiles || h->depth < 3 || !has_group(h, h->depth, kind[0])) return false;
+  if (h->tile_x < h->depth || h->tile_y < h->depth) return false;  // a single tile covers a group's reach
+  int n = 0, forced = 0;
+  for (size_t t = 0; t < near.size(); ++t)
+    if (near[t]) {
+      ++n;
+      forced += h->tile_off[t + 1] > h->tile_off[t];
+    }
+  return forced <= kStepMaxForced && n <= 2 * kStepMaxWork;
+}
+
 // Tiles for temporal blocking of depth d = h->depth on the current launch
 // shape: a tile is "near" if a marker stencil grown by d - 1 nodes reaches
 // it (a pass takes its first step over its tiles grown by d - 1 nodes, which
@@ -266,6 +289,7 @@ void fused_lists(btdf_t *h) {
   }
   for (int t = 0; t < ntiles; ++t)
     if (near[t]) edge[t] = 0;
+  h->beside = pass_beside(h, near);
   // Blocked tiles, level by level (the map lists the levels in order, each
   // group by its lower-left tile): rows of four tiles where the launch shape
   // has such a pass, then rows of two, then single tiles. A level lists its
@@ -280,6 +304,17 @@ void fused_lists(btdf_t *h) {
     taken[0][t] = near[t] || edge[t];
     taken[1][t] = near[t] || !edge[t];
   }
+  std::vector<char> single(ntiles, 0);
+  if (h->beside) {
+    // two levels: the largest groups, of tiles that border no near tile, and
+    // every other tile by itself (the near tiles' steps wait for these only)
+    h->gkind[1] = kGroup1x1;
+    h->gkind[2] = h->gkind[3] = kNoGroup;
+    for (int t = 0; t < ntiles; ++t)
+      for (int r = std::max(0, t / ntx - 1); r <= std::min(nty - 1, t / ntx + 1); ++r)
+        for (int c = std::max(0, t % ntx - 1); c <= std::min(ntx - 1, t % ntx + 1); ++c)
+          if (near[r * ntx + c]) single[t] = 1;
+  }
   for (int g = 0; g < kLevels; ++g) {
     const int code = h->gkind[g], w = code & 15, gh = (code >> 4) & 15;
     const size_t start = h->fmap.size();
@@ -291,7 +326,7 @@ void fused_lists(btdf_t *h) {
           const int t = b * ntx + a;
           bool ok = true;
           for (int r = 0; r < gh; ++r)
-            for (int k = 0; k < w; ++k) ok = ok && !tk[t + r * ntx + k];
+            for (int k = 0; k < w; ++k) ok = ok && !tk[t + r * ntx + k] && !(g == 0 && single[t + r * ntx + k]);
           if (!ok) {
             ++a;
             continue;
@@ -425,7 +460,7 @@ MoveParams make_move(const btdf_t *h) {
 // for launch shapes that have no such step.
 void step_items(btdf_t *h) {
   h->work.clear();
-  h->n_work[0] = h->n_work[1] = 0;
+  h->n_work[0] = h->n_work[1] = h->n_work_forced[0] = h->n_work_forced[1] = 0;
   if (!variant_has_step(h->variant) || h->owner || h->ntx > 0xffff || h->nty > 0x7fff) return;
   for (int near = 0; near < 2; ++near) {
     const size_t start = h->work.size();
@@ -436,6 +471,7 @@ void step_items(btdf_t *h) {
       const int t = tile(k), m0 = h->tile_off[t], m1 = h->tile_off[t + 1];
       if (m1 > m0) h->work.push_back({code(t), -1, m0, m1});
     }
+    h->n_work_forced[near] = (int)(h->work.size() - start);
     bool half = false;
     for (int k = 0; k < n; ++k) {
       const int t = tile(k);
@@ -806,7 +842,8 @@ StepWork step_work(const btdf_t *h, bool near) {
 
 bool one_launch(const btdf_t *h, bool near) {
   return variant_has_step(h->variant) && h->nm() > 0 && h->nf == 1 && h->method != BTDF_FORCING_IMPLICIT &&
-         h->plane * h->prec < (1LL << 32) && h->n_work[near] > 0 && h->n_work[near] <= kStepMaxWork;
+         h->plane * h->prec < (1LL << 32) && h->n_work[near] > 0 && h->n_work[near] <= kStepMaxWork &&
+         h->n_work_forced[near] <= kStepMaxForced;
 }
 
 int run_step(btdf_t *h, const LbmParams &p, const IbParams &ib, const void *A, void *B, bool near, hipStream_t s,
@@ -829,17 +866,31 @@ int run_step(btdf_t *h, const LbmParams &p, const IbParams &ib, const void *A, v
   return ok();
 }
 
-int finish_run(const IbParams &ib, hipStream_t s, StepRun *run) {
+// wait for a pass's large groups on the second stream, if they are there
+static int join_side(btdf_t *h, hipStream_t s, StepRun *run) {
+  if (!run->side) return ok();
+  HIPCHK(hipStreamWaitEvent(s, h->join_ev, 0));
+  run->side = false;
+  return ok();
+}
+
+// the body forces of the last step in the handle's history
+static int flush_forces(const IbParams &ib, hipStream_t s, StepRun *run) {
   if (!run->pending) return ok();
   HIPCHK(launch_step_flush(ib, run->link, s));
   run->pending = false;
   return ok();
 }
 
+int finish_run(btdf_t *h, const IbParams &ib, hipStream_t s, StepRun *run) {
+  const int rc = join_side(h, s, run);
+  return rc ? rc : flush_forces(ib, s, run);
+}
+
 // The marker kernel of a step in two launches. A one-launch step before it
 // has its body forces summed first.
 int step_markers(btdf_t *h, const LbmParams &p, const IbParams &ib, const void *A, hipStream_t s, StepRun *run) {
-  const int rc = finish_run(ib, s, run);
+  const int rc = flush_forces(ib, s, run);
   if (rc) return rc;
   HIPCHK(launch_ib(h->prec, A, p, ib, s));
   run->left--;
@@ -855,6 +906,7 @@ int enqueue_step(btdf_t *h, const LbmParams &p, const IbParams &ib, int src, hip
   void *B = h->ws + h->off_pop[1 - src];
   const bool one = one_launch(h, false);
   int rc;
+  if ((rc = join_side(h, s, run))) return rc;
   if (te) HIPCHK(hipEventRecord(te->ib0, s));
   if (!one && (rc = step_markers(h, p, ib, A, s, run))) return rc;
   if (te) HIPCHK(hipEventRecord(te->ib1, s));
@@ -883,7 +935,7 @@ int build_graph(btdf_t *h, const LbmParams &p, const IbParams &ib) {
   int rc = 0;
   StepRun run{h->graph_chunk};
   for (int k = 0; k < h->graph_chunk && rc == 0; ++k) rc = enqueue_step(h, p, ib, k & 1, h->cap_stream, nullptr, &run);
-  if (rc == 0) rc = finish_run(ib, h->cap_stream, &run);
+  if (rc == 0) rc = finish_run(h, ib, h->cap_stream, &run);
   hipError_t e = hipStreamEndCapture(h->cap_stream, &g);
   h->graph_depth = 1;
   if (rc) {
@@ -1233,7 +1285,7 @@ static int single_steps(btdf_t *h, const LbmParams &p, const IbParams &ib, int64
     h->cur ^= 1;
     h->steps++;
   }
-  return finish_run(ib, h->stream, &run);
+  return finish_run(h, ib, h->stream, &run);
 }
 
 // n steps from the current buffer: graphs of graph_chunk steps where they fit
@@ -1377,6 +1429,7 @@ static int enqueue_pair(btdf_t *h, const LbmParams &p, const IbParams &ib, hipSt
   const int *fm = h->at<int>(h->off_fmap);
   const unsigned char *near = h->at<unsigned char>(h->off_near);
   int rc;
+  if ((rc = join_side(h, s, run))) return rc;
   if (ev && ev[0]) HIPCHK(hipEventRecord(ev[0], s));
   if ((rc = near_markers(h, p, ib, A, s, run))) return rc;
   if (ev && ev[1]) HIPCHK(hipEventRecord(ev[1], s));
@@ -1405,6 +1458,42 @@ static int fork_side(btdf_t *h, hipStream_t s) {
   return ok();
 }
 
+// d steps with the pass's large groups (level 0) on the second stream beside
+// the near tiles' steps, which run after the single tiles (level 1) that give
+// them their neighbours' states. X[k]: the near tiles' state n + k, X[d] the
+// pass's destination; pass(g, stream) launches level g.
+//
+// The two streams wait for each other only where one reads or overwrites
+// what the other made. The large groups border no near tile, so within the
+// few nodes a group reads around itself lie only large groups and single
+// tiles: a pass's large groups follow the pass before's single tiles, and a
+// pass's single tiles follow the pass before's large groups. Neither waits at
+// a pass's end, and the near tiles' first step needs neither.
+static int enqueue_beside(btdf_t *h, const LbmParams &p, const IbParams &ib, hipStream_t s, StepRun *run, int d,
+                          const void *A, void *const *X, const std::function<hipError_t(int, hipStream_t)> &pass) {
+  int rc;
+  if (!run->side) {
+    if ((rc = fork_side(h, s))) return rc;
+  } else {
+    HIPCHK(hipStreamWaitEvent(h->side, h->fork_ev, 0));  // the pass before's single tiles
+  }
+  for (int k = 0; k < d; ++k) {
+    const void *src = k ? X[k] : A;
+    if ((rc = near_markers(h, p, ib, src, s, run))) return rc;
+    if ((rc = near_step(h, p, ib, src, X[k + 1], s, run))) return rc;
+    if (k > 0) continue;
+    if ((rc = join_side(h, s, run))) return rc;
+    HIPCHK(pass(1, s));
+    HIPCHK(pass(0, h->side));
+    HIPCHK(hipEventRecord(h->join_ev, h->side));
+    HIPCHK(hipEventRecord(h->fork_ev, s));
+    run->side = true;
+  }
+  h->cur ^= 1;
+  h->steps += d;
+  return ok();
+}
+
 // three steps from buffer cur into 1 - cur (three-step blocking): as a pair,
 // with the near tiles' states n+1 and n+2 in X1 and X2 and the marker kernel
 // before each of their steps. The three-step pass writes both rings, so it
@@ -1422,6 +1511,15 @@ static int enqueue_triple(btdf_t *h, const LbmParams &p, const IbParams &ib, hip
   const int *fm = h->at<int>(h->off_fmap);
   const unsigned char *near = h->at<unsigned char>(h->off_near);
   int rc;
+  if (h->beside && !ev) {
+    void *X[4] = {nullptr, X1, X2, B};
+    const auto pass = [&](int g, hipStream_t st) -> hipError_t {
+      if (!h->n_grp[g]) return hipSuccess;
+      return launch_lbm3(h->prec, h->variant, h->gkind[g], A, B, p, fm + h->grp_start(g), h->n_grp[g], X1, X2, near, st);
+    };
+    return enqueue_beside(h, p, ib, s, run, 3, A, X, pass);
+  }
+  if ((rc = join_side(h, s, run))) return rc;
   if (ev && ev[0]) HIPCHK(hipEventRecord(ev[0], s));
   if ((rc = near_markers(h, p, ib, A, s, run))) return rc;
   if (ev && ev[1]) HIPCHK(hipEventRecord(ev[1], s));
@@ -1473,11 +1571,22 @@ static int enqueue_deep(btdf_t *h, const LbmParams &p, const IbParams &ib, hipSt
   const void *A = h->ws + h->off_pop[h->cur];
   void *B = h->ws + h->off_pop[1 - h->cur];
   // (X1 .. X4 are consecutive population buffers, which the pass addresses from X1)
-  void *X[5] = {nullptr, h->ws + h->off_pop3, h->ws + h->off_pop4, h->ws + h->off_pop5, h->ws + h->off_pop6};
+  void *X[6] = {nullptr, h->ws + h->off_pop3, h->ws + h->off_pop4, h->ws + h->off_pop5, h->ws + h->off_pop6};
   const int *fm = h->at<int>(h->off_fmap);
   const unsigned *rwin = h->at<unsigned>(h->off_rwin);
   int rc;
   auto mark = [&](int k) -> hipError_t { return ev && ev[k] ? hipEventRecord(ev[k], s) : hipSuccess; };
+  if (h->beside && !ev) {
+    X[d] = B;
+    const auto pass = [&](int g, hipStream_t st) -> hipError_t {
+      if (!h->n_grp[g]) return hipSuccess;
+      // (one launch per level: a single tile without near neighbours has an empty window)
+      return launch_lbm_deep(h->prec, h->variant, d, h->gkind[g], A, B, p, fm + h->grp_start(g), h->n_grp[g],
+                             g ? h->n_grp[g] : 0, X[1], rwin + h->grp_start(g), st);
+    };
+    return enqueue_beside(h, p, ib, s, run, d, A, X, pass);
+  }
+  if ((rc = join_side(h, s, run))) return rc;
   HIPCHK(mark(0));
   if ((rc = near_markers(h, p, ib, A, s, run))) return rc;
   HIPCHK(mark(1));
@@ -1535,7 +1644,7 @@ static int build_pass_graph(btdf_t *h, const LbmParams &p, const IbParams &ib, i
   int rc = 0;
   StepRun run{(int64_t)passes * h->depth};
   for (int k = 0; k < passes && rc == 0; ++k) rc = enqueue_pass(h, p, ib, h->cap_stream, nullptr, &run);
-  if (rc == 0) rc = finish_run(ib, h->cap_stream, &run);
+  if (rc == 0) rc = finish_run(h, ib, h->cap_stream, &run);
   hipError_t e = hipStreamEndCapture(h->cap_stream, &g);
   h->cur = cur;  // capturing ran nothing
   h->steps = steps;
@@ -1551,6 +1660,28 @@ static int build_pass_graph(btdf_t *h, const LbmParams &p, const IbParams &ib, i
     return fail(BTDF_EDEVICE, "hipGraphInstantiate: %s", hipGetErrorString(e));
   }
   h->graph_depth = h->depth;
+  return ok();
+}
+
+// left steps with temporal blocking: whole passes, then what is left over
+static int blocked_steps(btdf_t *h, const LbmParams &p, const IbParams &ib, int64_t left, StepRun *run) {
+  const int d = h->depth;
+  int rc;
+  for (; left >= d; left -= d)
+    if ((rc = enqueue_pass(h, p, ib, h->stream, nullptr, run))) return rc;
+  if (left >= 3 && remainder_triple(h)) {
+    if ((rc = enqueue_triple(h, p, ib, h->stream, nullptr, run))) return rc;
+    left -= 3;
+  }
+  if (left == 2 && remainder_pair(h)) {
+    if ((rc = enqueue_pair(h, p, ib, h->stream, nullptr, run))) return rc;
+    left = 0;
+  }
+  for (; left > 0; --left) {
+    if ((rc = enqueue_step(h, p, ib, h->cur, h->stream, nullptr, run))) return rc;
+    h->cur ^= 1;
+    h->steps++;
+  }
   return ok();
 }
 
@@ -1576,22 +1707,9 @@ static int run_blocked(btdf_t *h, const LbmParams &p, const IbParams &ib, int64_
     }
   }
   StepRun run{left};
-  for (; left >= d; left -= d)
-    if ((rc = enqueue_pass(h, p, ib, h->stream, nullptr, &run))) return rc;
-  if (left >= 3 && remainder_triple(h)) {
-    if ((rc = enqueue_triple(h, p, ib, h->stream, nullptr, &run))) return rc;
-    left -= 3;
-  }
-  if (left == 2 && remainder_pair(h)) {
-    if ((rc = enqueue_pair(h, p, ib, h->stream, nullptr, &run))) return rc;
-    left = 0;
-  }
-  for (; left > 0; --left) {
-    if ((rc = enqueue_step(h, p, ib, h->cur, h->stream, nullptr, &run))) return rc;
-    h->cur ^= 1;
-    h->steps++;
-  }
-  return finish_run(ib, h->stream, &run);
+  rc = blocked_steps(h, p, ib, left, &run);
+  const int end = finish_run(h, ib, h->stream, &run);  // (also after a failure: the second stream is joined)
+  return rc ? rc : end;
 }
 
 static bool blocking_active(const btdf_t *h) {
@@ -1748,7 +1866,7 @@ static int timed_impl(btdf_t *h, int64_t n, double *out, bool pass_only = false)
     }
     done += (int64_t)dk * m;
   }
-  if (rc || (rc = finish_run(ib, h->stream, &run))) return rc;
+  if (rc || (rc = finish_run(h, ib, h->stream, &run))) return rc;
   HIPCHK(hipStreamSynchronize(h->stream));
   h->stepped = true;
   out[0] = h->nb() ? tib / (double)n : 0.0;

@@ -99,12 +99,13 @@ struct btdf_sim {
   int n_grp[btdf::kLevels] = {};  // groups per level
   int n_edge[btdf::kLevels] = {};  // of those, edge groups (first in the level's list)
   int n_ring[btdf::kLevels] = {};  // passes of four or five steps: groups bordering a near tile (listed first)
+  bool beside = false;             // the pass's large groups run beside the near tiles' steps (pass_beside)
   long long pass_nodes = 0;        // grid nodes in the blocked pass (partial tiles counted by their nodes)
   int n_near = 0;
   // one-launch steps: what each workgroup does, over all tiles, then over the
   // pass's near tiles
   std::vector<btdf::StepItem> work;
-  int n_work[2] = {0, 0};
+  int n_work[2] = {0, 0}, n_work_forced[2] = {0, 0};  // entries, and those with markers
   int n_groups() const {
     int k = 0;
     for (int i = 0; i < btdf::kLevels; ++i) k += n_grp[i];
@@ -214,8 +215,15 @@ constexpr long long kBlockMinNodes = 1ll << 20;
 constexpr int kDefaultDepth = 5;
 // width in tile columns of the bands down which groups two tiles tall are launched
 constexpr int kSquareBand = 32;
-// most workgroups of a one-launch step
-constexpr int kStepMaxWork = 2048;
+// Most tiles with markers, and most workgroups, of a one-launch step: where
+// two launches in turn are as fast. Forming a marker in every tile it touches
+// costs 2.5 times the marker kernel's reads, so it pays only while tiles are
+// too few to fill the GPU: per step 17.6 us against 26.6 on 1024^2 with 31
+// cylinders of D = 24 (350 tiles), 42.8 against 44.1 on 2048^2 with 125 (1400,
+// blocked passes), 80.8 against 77.0 on 3072^2 with 280 (3100); without many
+// markers 37.2 against 45.2 us on 2000x1400 and equal at 88 on 3000x2000
+// (11 800 workgroups; all FP32, FP64 alike).
+constexpr int kStepMaxForced = 1536, kStepMaxWork = 8192;
 std::string forcing_setup(btdf_t *h);
 LbmParams make_params(const btdf_t *h);
 IbParams make_ib(const btdf_t *h);
@@ -237,6 +245,7 @@ struct StepEvents {
 struct StepRun {
   int64_t left = 0;        // steps still to enqueue
   bool pending = false;    // the last one's body forces are not summed yet
+  bool side = false;       // a pass's large groups are on the second stream (join_ev ends them)
   StepLink link{};
 };
 // Whether a step takes one launch, over all tiles or (near) over the blocked
@@ -246,7 +255,7 @@ bool one_launch(const btdf_t *h, bool near);
 int run_step(btdf_t *h, const LbmParams &p, const IbParams &ib, const void *A, void *B, bool near, hipStream_t s,
              StepRun *run);
 StepWork step_work(const btdf_t *h, bool near);
-int finish_run(const IbParams &ib, hipStream_t s, StepRun *run);
+int finish_run(btdf_t *h, const IbParams &ib, hipStream_t s, StepRun *run);
 // one step from population buffer src into the other, on stream s
 int enqueue_step(btdf_t *h, const LbmParams &p, const IbParams &ib, int src, hipStream_t s,
                  const StepEvents *te, StepRun *run);
