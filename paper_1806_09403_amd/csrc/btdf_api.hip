@@ -821,14 +821,56 @@ int read_ctl(btdf_t *h, long long *ctr, int *flag) {
   return ok();
 }
 
+static int flag_status(int flag) {
+  if (flag > 0) return fail(BTDF_EUNSTABLE, "unstable: marker of body %d (non-finite force or |u*| > 0.3)", flag - 1);
+  if (flag < 0) return fail(BTDF_EUNSTABLE, "unstable: non-positive or non-finite density at a node");
+  return ok();
+}
+
 int check_flag(btdf_t *h) {
   long long ctr;
   int flag;
   int rc = read_ctl(h, &ctr, &flag);
-  if (rc) return rc;
-  if (flag > 0) return fail(BTDF_EUNSTABLE, "unstable: marker of body %d (non-finite force or |u*| > 0.3)", flag - 1);
-  if (flag < 0) return fail(BTDF_EUNSTABLE, "unstable: non-positive or non-finite density at a node");
-  return ok();
+  return rc ? rc : flag_status(flag);
+}
+
+// most bytes of forces that come by the report kernel
+static constexpr size_t kReportBytes = 64 * 1024;
+
+// The body forces of cnt steps from step first (all in the ring) to out, and
+// the status of the run. Waits for the handle's stream. A few kilobytes come
+// with the flag in one launch that writes pinned memory, and one wait; as a
+// copy each, with a wait before and between, they were four round trips (a
+// loop of set_marker_velocity, step(1), forces on 97x61: 77 us a turn then,
+// 29 now, of which btdf_set_marker_velocity's launch in the place of two
+// copies and a wait is a third).
+static int read_forces(btdf_t *h, int64_t first, int64_t cnt, double *out) {
+  const int row = 3 * h->nb();
+  const size_t bytes = (size_t)cnt * row * sizeof(double), need = bytes + sizeof(double);
+  const double *hist = h->at<double>(h->off_hist);
+  if (need <= kReportBytes && ++h->reports > 1) {
+    if (h->pin_bytes < need) {
+      if (h->pin) HIPCHK(hipHostFree(h->pin));
+      h->pin = nullptr;
+      h->pin_bytes = 0;
+      const size_t cap = (need + 4095) / 4096 * 4096;
+      HIPCHK(hipHostMalloc((void **)&h->pin, cap, hipHostMallocDefault));
+      h->pin_bytes = cap;
+    }
+    HIPCHK(launch_report(hist, h->hist_cap, row, first, (int)cnt, h->at<int>(h->off_ctl + 8), h->pin, h->stream));
+    HIPCHK(hipStreamSynchronize(h->stream));
+    std::memcpy(out, h->pin + 1, bytes);
+    return flag_status((int)h->pin[0]);
+  }
+  HIPCHK(hipStreamSynchronize(h->stream));
+  for (int64_t k = 0; k < cnt;) {
+    const int64_t slot = (first + k) % h->hist_cap;
+    const int64_t run = std::min<int64_t>(cnt - k, h->hist_cap - slot);
+    HIPCHK(hipMemcpy(out + (size_t)k * row, hist + (size_t)slot * row, (size_t)run * row * sizeof(double),
+                     hipMemcpyDeviceToHost));
+    k += run;
+  }
+  return check_flag(h);
 }
 
 int clear_flag(btdf_t *h) {
@@ -1074,6 +1116,7 @@ int destroy_impl(btdf_t *h) {
   if (h->fork_ev) (void)hipEventDestroy(h->fork_ev);
   if (h->join_ev) (void)hipEventDestroy(h->join_ev);
   h->tev.release();
+  if (h->pin) (void)hipHostFree(h->pin);
   if (h->ws && h->ws_owned) (void)hipFree(h->ws);
   delete h;
   return rc;
@@ -1262,6 +1305,15 @@ int btdf_set_marker_velocity(btdf_t *h, int body, const double *uv) {
     if (h->ws && h->device_ok) {
       const size_t M = (size_t)std::max(h->nm(), 1), d = sizeof(double);
       int rc;
+      if (l1 - l0 <= MarkerUv::kMax) {  // small bodies: in the launch itself, nothing to wait for
+        MarkerUv a;
+        a.n = l1 - l0;
+        std::copy(h->U.begin() + l0, h->U.begin() + l1, a.u);
+        std::copy(h->V.begin() + l0, h->V.begin() + l1, a.v);
+        double *mk = h->at<double>(h->off_mk);
+        HIPCHK(launch_marker_uv(a, mk + 2 * M + l0, mk + 3 * M + l0, h->stream));
+        return ok();
+      }
       if ((rc = upload(h, h->off_mk + 2 * M * d + l0 * d, h->U.data() + l0, (l1 - l0) * d))) return rc;
       if ((rc = upload(h, h->off_mk + 3 * M * d + l0 * d, h->V.data() + l0, (l1 - l0) * d))) return rc;
       HIPCHK(hipStreamSynchronize(h->stream));
@@ -1959,17 +2011,9 @@ int btdf_forces(btdf_t *h, double *out, int cap_bodies) {
     }
     int rc = ensure_device(h);
     if (rc) return rc;
-    HIPCHK(hipStreamSynchronize(h->stream));
-    if (nb > 0) {
-      const long long slot = (h->steps - 1) % h->hist_cap;
-      if (h->steps <= h->forces_from) {
-        // no step since the body set changed or a state was loaded
-        for (int k = 0; k < 3 * nb; ++k) out[k] = 0.0;
-      } else {
-        HIPCHK(hipMemcpy(out, h->ws + h->off_hist + (size_t)slot * nb * 3 * sizeof(double),
-                         (size_t)nb * 3 * sizeof(double), hipMemcpyDeviceToHost));
-      }
-    }
+    if (nb > 0 && h->steps > h->forces_from) return read_forces(h, h->steps - 1, 1, out);
+    // no step since the body set changed or a state was loaded
+    for (int k = 0; k < 3 * nb; ++k) out[k] = 0.0;
     return check_flag(h);
   });
 }
@@ -1985,23 +2029,15 @@ int btdf_force_history(btdf_t *h, double *out, int64_t max_steps, int64_t *n_wri
     }
     int rc = ensure_device(h);
     if (rc) return rc;
-    HIPCHK(hipStreamSynchronize(h->stream));
     const int64_t pending = h->steps - std::max(h->hist_read, h->forces_from);
     const int64_t avail = std::min<int64_t>(pending, h->hist_cap);
     const int64_t first = h->steps - avail;
     const int64_t cnt = std::min<int64_t>(avail, max_steps);
-    const size_t row = (size_t)nb * 3 * sizeof(double);
-    int64_t k = 0;
-    while (k < cnt) {
-      const int64_t slot = (first + k) % h->hist_cap;
-      const int64_t run = std::min<int64_t>(cnt - k, h->hist_cap - slot);
-      HIPCHK(hipMemcpy((char *)out + (size_t)k * row, h->ws + h->off_hist + (size_t)slot * row,
-                       (size_t)run * row, hipMemcpyDeviceToHost));
-      k += run;
-    }
+    rc = cnt > 0 ? read_forces(h, first, cnt, out) : check_flag(h);
+    if (rc && rc != BTDF_EUNSTABLE) return rc;  // (the values of an unstable run are written all the same)
     h->hist_read = first + cnt;
     *n_written = cnt;
-    return check_flag(h);
+    return rc;
   });
 }
 
@@ -2051,10 +2087,12 @@ int btdf_get_populations(btdf_t *h, double *dst) {
     const size_t n = (size_t)h->nx * h->ny;
     double *st = h->at<double>(h->off_pop[1 - h->cur]);
     LbmParams p = make_params(h);
-    for (int q = 0; q < 9; ++q) {
-      HIPCHK(launch_plane_to_f64(h->prec, h->ws + h->off_pop[h->cur], p, q, st, h->stream));
+    const int per = h->prec == 8 ? 9 : 4;  // planes the staging buffer holds in FP64
+    for (int q = 0; q < 9; q += per) {
+      const int nq = std::min(per, 9 - q);
+      HIPCHK(launch_pops_to_f64(h->prec, h->ws + h->off_pop[h->cur], p, q, nq, st, h->stream));
       HIPCHK(hipStreamSynchronize(h->stream));
-      HIPCHK(hipMemcpy(dst + (size_t)q * n, st, n * sizeof(double), hipMemcpyDeviceToHost));
+      HIPCHK(hipMemcpy(dst + (size_t)q * n, st, nq * n * sizeof(double), hipMemcpyDeviceToHost));
     }
     return ok();
   });
@@ -2068,10 +2106,11 @@ int btdf_set_populations(btdf_t *h, const double *src) {
     const size_t n = (size_t)h->nx * h->ny;
     double *st = h->at<double>(h->off_pop[1 - h->cur]);
     LbmParams p = make_params(h);
-    for (int q = 0; q < 9; ++q) {
-      HIPCHK(hipMemcpyAsync(st, src + (size_t)q * n, n * sizeof(double), hipMemcpyHostToDevice, h->stream));
-      HIPCHK(launch_f64_to_plane(h->prec, h->ws + h->off_pop[h->cur], p, q, st, h->stream));
-      HIPCHK(hipStreamSynchronize(h->stream));
+    const int per = h->prec == 8 ? 9 : 4;  // planes the staging buffer holds in FP64
+    for (int q = 0; q < 9; q += per) {
+      const int nq = std::min(per, 9 - q);
+      HIPCHK(hipMemcpyAsync(st, src + (size_t)q * n, nq * n * sizeof(double), hipMemcpyHostToDevice, h->stream));
+      HIPCHK(launch_f64_to_pops(h->prec, h->ws + h->off_pop[h->cur], p, q, nq, st, h->stream));
     }
     h->stepped = false;
     if ((rc = clear_flag(h))) return rc;
@@ -2103,11 +2142,8 @@ int btdf_get_populations_to(btdf_t *h, void *dst, int dst_on_device) {
     int rc = ensure_device(h);
     if (rc) return rc;
     if ((rc = check_device_ptr(h, dst))) return rc;
-    const size_t n = (size_t)h->nx * h->ny;
     LbmParams p = make_params(h);
-    double *out = static_cast<double *>(dst);
-    for (int q = 0; q < 9; ++q)
-      HIPCHK(launch_plane_to_f64(h->prec, h->ws + h->off_pop[h->cur], p, q, out + (size_t)q * n, h->stream));
+    HIPCHK(launch_pops_to_f64(h->prec, h->ws + h->off_pop[h->cur], p, 0, 9, static_cast<double *>(dst), h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
     return ok();
   });
@@ -2120,11 +2156,8 @@ int btdf_set_populations_from(btdf_t *h, const void *src, int src_on_device) {
     int rc = ensure_device(h);
     if (rc) return rc;
     if ((rc = check_device_ptr(h, src))) return rc;
-    const size_t n = (size_t)h->nx * h->ny;
     LbmParams p = make_params(h);
-    const double *in = static_cast<const double *>(src);
-    for (int q = 0; q < 9; ++q)
-      HIPCHK(launch_f64_to_plane(h->prec, h->ws + h->off_pop[h->cur], p, q, in + (size_t)q * n, h->stream));
+    HIPCHK(launch_f64_to_pops(h->prec, h->ws + h->off_pop[h->cur], p, 0, 9, static_cast<const double *>(src), h->stream));
     h->stepped = false;
     if ((rc = clear_flag(h))) return rc;
     HIPCHK(hipStreamSynchronize(h->stream));

@@ -265,6 +265,13 @@ struct StepWork {
   int count;
 };
 
+// the velocities of a body's markers as a kernel argument (btdf_set_marker_velocity)
+struct MarkerUv {
+  static constexpr int kMax = 128;
+  int n;
+  double u[kMax], v[kMax];
+};
+
 // rigid body motion, one workgroup per body after each step
 struct MoveParams {
   int nb;

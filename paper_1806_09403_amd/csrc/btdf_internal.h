@@ -149,6 +149,11 @@ struct btdf_sim {
   hipStream_t side = nullptr;
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
   btdf_event_pool tev;  // events of the timed stepping calls
+  // pinned host memory the force calls' report kernel writes (from the second
+  // such call on: a program that asks once does not pay for it)
+  double *pin = nullptr;
+  size_t pin_bytes = 0;
+  int reports = 0;
 
   int nb() const { return (int)cx.size(); }
   bool any_moving() const {

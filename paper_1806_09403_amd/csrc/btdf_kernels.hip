@@ -317,24 +317,73 @@ __global__ void init_uniform_kernel(T *__restrict__ A, LbmParams p, double r, do
   }
 }
 
-// one population plane <-> packed FP64 full values
-template <typename T>
-__global__ void plane_to_f64_kernel(const T *__restrict__ A, LbmParams p, int q, double *__restrict__ out) {
-  const long long n = (long long)p.nx * p.ny;
-  for (long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x; k < n;
-       k += (long long)gridDim.x * blockDim.x) {
-    const int y = (int)(k / p.nx), x = (int)(k - (long long)y * p.nx);
-    out[k] = (double)A[(long long)q * p.plane + (long long)y * p.pitch + x] + ref_c(q, p.urx, p.ury);
-  }
+// Planes q0 .. q0 + gridDim.y of the populations <-> packed FP64 full values,
+// one plane after the other. Bound by memory (one population read or written
+// and one FP64 value the other way), so all planes go in one launch, and
+// where rows and both arrays allow it (V = 2: even rows, aligned pairs) a
+// thread moves two neighbours, one 16-byte access on the FP64 side; otherwise
+// one node. One pair per thread and no loop: the 8192^2 FP32 lattice takes
+// 1.12 ms (6.5 TB/s), 1.59 a node per thread, 1.22 in quadruples, 1.27 and
+// more with several per thread or a capped grid. (9 launches of a plane each
+// took 1.56 ms; on small lattices they cost 2.6 us apiece.)
+template <typename T, int V>
+__global__ __launch_bounds__(256) void pops_to_f64_kernel(const T *__restrict__ A, LbmParams p, int q0,
+                                                          double *__restrict__ out) {
+  typedef T vt __attribute__((ext_vector_type(V)));
+  typedef double vd __attribute__((ext_vector_type(V)));
+  const unsigned w = (unsigned)p.nx / V, n = w * (unsigned)p.ny;
+  const int q = q0 + (int)blockIdx.y;
+  const T *src = A + (long long)q * p.plane;
+  double *dst = out + (long long)blockIdx.y * p.nx * p.ny;
+  const double c = ref_c(q, p.urx, p.ury);
+  const unsigned k = blockIdx.x * 256u + threadIdx.x;
+  if (k >= n) return;
+  const unsigned y = k / w, x = (k - y * w) * V;
+  const vt v = __builtin_nontemporal_load(reinterpret_cast<const vt *>(src + (long long)y * p.pitch + x));
+  vd o;
+#pragma unroll
+  for (int u = 0; u < V; ++u) o[u] = (double)v[u] + c;
+  __builtin_nontemporal_store(o, reinterpret_cast<vd *>(dst + (long long)k * V));
 }
 
-template <typename T>
-__global__ void f64_to_plane_kernel(T *__restrict__ A, LbmParams p, int q, const double *__restrict__ in) {
-  const long long n = (long long)p.nx * p.ny;
-  for (long long k = blockIdx.x * (long long)blockDim.x + threadIdx.x; k < n;
-       k += (long long)gridDim.x * blockDim.x) {
-    const int y = (int)(k / p.nx), x = (int)(k - (long long)y * p.nx);
-    A[(long long)q * p.plane + (long long)y * p.pitch + x] = (T)(in[k] - ref_c(q, p.urx, p.ury));
+template <typename T, int V>
+__global__ __launch_bounds__(256) void f64_to_pops_kernel(T *__restrict__ A, LbmParams p, int q0,
+                                                          const double *__restrict__ in) {
+  typedef T vt __attribute__((ext_vector_type(V)));
+  typedef double vd __attribute__((ext_vector_type(V)));
+  const unsigned w = (unsigned)p.nx / V, n = w * (unsigned)p.ny;
+  const int q = q0 + (int)blockIdx.y;
+  T *dst = A + (long long)q * p.plane;
+  const double *src = in + (long long)blockIdx.y * p.nx * p.ny;
+  const double c = ref_c(q, p.urx, p.ury);
+  const unsigned k = blockIdx.x * 256u + threadIdx.x;
+  if (k >= n) return;
+  const unsigned y = k / w, x = (k - y * w) * V;
+  const vd v = __builtin_nontemporal_load(reinterpret_cast<const vd *>(src + (long long)k * V));
+  vt o;
+#pragma unroll
+  for (int u = 0; u < V; ++u) o[u] = (T)(v[u] - c);
+  *reinterpret_cast<vt *>(dst + (long long)y * p.pitch + x) = o;
+}
+
+// The body forces of cnt steps from step first (ring entries), and the
+// instability flag, to host memory the device can write: host[0] holds the
+// flag, then the values.
+__global__ __launch_bounds__(256) void report_kernel(const double *__restrict__ hist, int cap, int row, long long first,
+                                                     int cnt, const int *flag, double *__restrict__ host) {
+  for (int k = (int)threadIdx.x; k < cnt * row; k += 256) {
+    const int s = k / row;
+    host[1 + k] = hist[((first + s) % cap) * row + (k - s * row)];
+  }
+  if (threadIdx.x == 0) host[0] = (double)flag[0];
+}
+
+// prescribed velocities of the n markers from l0, handed over in the launch
+__global__ void marker_uv_kernel(MarkerUv a, double *__restrict__ U, double *__restrict__ V) {
+  const int i = (int)threadIdx.x;
+  if (i < a.n) {
+    U[i] = a.u[i];
+    V[i] = a.v[i];
   }
 }
 
@@ -1216,25 +1265,52 @@ hipError_t launch_init_eq(int prec, void *A, const LbmParams &p, const double *r
   return hipGetLastError();
 }
 
-hipError_t launch_plane_to_f64(int prec, const void *A, const LbmParams &p, int q, double *out,
-                               hipStream_t s) {
-  if (prec == 4)
-    hipLaunchKernelGGL(plane_to_f64_kernel<float>, dim3(grid_for<float>(p)), dim3(256), 0, s,
-                       (const float *)A, p, q, out);
+// whether rows of the populations and of a packed FP64 array can be moved in pairs
+static bool pairs(int prec, const LbmParams &p, const void *pops, const void *f64) {
+  return p.nx % 2 == 0 && p.pitch % 2 == 0 && p.plane % 2 == 0 && (uintptr_t)pops % (2 * prec) == 0 &&
+         (uintptr_t)f64 % 16 == 0;
+}
+
+hipError_t launch_pops_to_f64(int prec, const void *A, const LbmParams &p, int q0, int nq, double *out,
+                              hipStream_t s) {
+  const bool v = pairs(prec, p, A, out);
+  const long long n = (long long)p.nx * p.ny / (v ? 2 : 1);
+  const dim3 g((unsigned)((n + 255) / 256), nq);
+  if (prec == 4 && v)
+    hipLaunchKernelGGL((pops_to_f64_kernel<float, 2>), g, dim3(256), 0, s, (const float *)A, p, q0, out);
+  else if (prec == 4)
+    hipLaunchKernelGGL((pops_to_f64_kernel<float, 1>), g, dim3(256), 0, s, (const float *)A, p, q0, out);
+  else if (v)
+    hipLaunchKernelGGL((pops_to_f64_kernel<double, 2>), g, dim3(256), 0, s, (const double *)A, p, q0, out);
   else
-    hipLaunchKernelGGL(plane_to_f64_kernel<double>, dim3(grid_for<double>(p)), dim3(256), 0, s,
-                       (const double *)A, p, q, out);
+    hipLaunchKernelGGL((pops_to_f64_kernel<double, 1>), g, dim3(256), 0, s, (const double *)A, p, q0, out);
   return hipGetLastError();
 }
 
-hipError_t launch_f64_to_plane(int prec, void *A, const LbmParams &p, int q, const double *in,
-                               hipStream_t s) {
-  if (prec == 4)
-    hipLaunchKernelGGL(f64_to_plane_kernel<float>, dim3(grid_for<float>(p)), dim3(256), 0, s,
-                       (float *)A, p, q, in);
+hipError_t launch_f64_to_pops(int prec, void *A, const LbmParams &p, int q0, int nq, const double *in,
+                              hipStream_t s) {
+  const bool v = pairs(prec, p, A, in);
+  const long long n = (long long)p.nx * p.ny / (v ? 2 : 1);
+  const dim3 g((unsigned)((n + 255) / 256), nq);
+  if (prec == 4 && v)
+    hipLaunchKernelGGL((f64_to_pops_kernel<float, 2>), g, dim3(256), 0, s, (float *)A, p, q0, in);
+  else if (prec == 4)
+    hipLaunchKernelGGL((f64_to_pops_kernel<float, 1>), g, dim3(256), 0, s, (float *)A, p, q0, in);
+  else if (v)
+    hipLaunchKernelGGL((f64_to_pops_kernel<double, 2>), g, dim3(256), 0, s, (double *)A, p, q0, in);
   else
-    hipLaunchKernelGGL(f64_to_plane_kernel<double>, dim3(grid_for<double>(p)), dim3(256), 0, s,
-                       (double *)A, p, q, in);
+    hipLaunchKernelGGL((f64_to_pops_kernel<double, 1>), g, dim3(256), 0, s, (double *)A, p, q0, in);
+  return hipGetLastError();
+}
+
+hipError_t launch_report(const double *hist, int cap, int row, long long first, int cnt, const int *flag, double *host,
+                         hipStream_t s) {
+  hipLaunchKernelGGL(report_kernel, dim3(1), dim3(256), 0, s, hist, cap, row, first, cnt, flag, host);
+  return hipGetLastError();
+}
+
+hipError_t launch_marker_uv(const MarkerUv &a, double *U, double *V, hipStream_t s) {
+  hipLaunchKernelGGL(marker_uv_kernel, dim3(1), dim3(MarkerUv::kMax), 0, s, a, U, V);
   return hipGetLastError();
 }
 

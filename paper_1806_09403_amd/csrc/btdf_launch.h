@@ -93,10 +93,15 @@ hipError_t launch_init_uniform(int prec, void *A, const LbmParams &p, double r, 
                                hipStream_t s);
 hipError_t launch_init_eq(int prec, void *A, const LbmParams &p, const double *rho, const double *ux,
                           const double *uy, double rho0, int per_node_rho, hipStream_t s);
-hipError_t launch_plane_to_f64(int prec, const void *A, const LbmParams &p, int q, double *out,
-                               hipStream_t s);
-hipError_t launch_f64_to_plane(int prec, void *A, const LbmParams &p, int q, const double *in,
-                               hipStream_t s);
+// population planes q0 .. q0 + nq to and from packed FP64 planes
+hipError_t launch_pops_to_f64(int prec, const void *A, const LbmParams &p, int q0, int nq, double *out,
+                              hipStream_t s);
+hipError_t launch_f64_to_pops(int prec, void *A, const LbmParams &p, int q0, int nq, const double *in,
+                              hipStream_t s);
+// the body forces of cnt steps and the instability flag to pinned host memory
+hipError_t launch_report(const double *hist, int cap, int row, long long first, int cnt, const int *flag, double *host,
+                         hipStream_t s);
+hipError_t launch_marker_uv(const MarkerUv &a, double *U, double *V, hipStream_t s);
 hipError_t launch_macro(int prec, const void *A, const LbmParams &p, double *rho, double *ux, double *uy,
                         hipStream_t s);
 
