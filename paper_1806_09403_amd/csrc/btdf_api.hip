@@ -455,6 +455,25 @@ MoveParams make_move(const btdf_t *h) {
   return mp;
 }
 
+// Whether the marker forces are formed body by body (body_kernel): the
+// implicit method, or several passes when no marker shares a stencil node with
+// another body's, on bodies of at most kBodyMax markers. (Also sets max_body.)
+bool bodies_apart(btdf_t *h) {
+  const bool implicit = h->method == BTDF_FORCING_IMPLICIT;
+  if ((!implicit && h->nf < 2) || h->nb() == 0) return false;
+  int most = 0;
+  for (int b = 0; b < h->nb(); ++b) most = std::max(most, h->off[b + 1] - h->off[b]);
+  if (most > kBodyMax) return false;
+  h->max_body = most;
+  if (implicit) return true;
+  for (int b = 0; b < h->nb(); ++b)
+    for (int e = h->cover_off[16 * (size_t)h->off[b]]; e < h->cover_off[16 * (size_t)h->off[b + 1]]; ++e) {
+      const int m = h->cover_list[e] >> 4;
+      if (m < h->off[b] || m >= h->off[b + 1]) return false;
+    }
+  return true;
+}
+
 // The work lists of one-launch steps: the tiles with markers one per entry,
 // then the others two per entry, over all tiles and over the near tiles. None
 // for launch shapes that have no such step.
@@ -566,6 +585,7 @@ void compute_layout(btdf_t *h) {
   o = align256(o + (h->nf > 1 ? 4 * (size_t)std::max(nm, 1) * sizeof(double) : 0));
   // implicit forcing: one inverse matrix per body; RKPM: nothing beyond the marker factors
   h->method_err = forcing_setup(h);
+  h->own_bodies = bodies_apart(h);
   h->off_moff = o;
   o = align256(o + h->minv_off.size() * sizeof(long long));
   h->off_minv = o;
@@ -882,10 +902,14 @@ StepWork step_work(const btdf_t *h, bool near) {
   return StepWork{h->at<StepItem>(h->off_work) + (near ? h->n_work[0] : 0), h->n_work[near]};
 }
 
+// whether a step over these tiles goes through the step kernel's work items
+static bool few_tiles(const btdf_t *h, bool near) {
+  return variant_has_step(h->variant) && h->plane * h->prec < (1LL << 32) && h->n_work[near] > 0 &&
+         h->n_work[near] <= kStepMaxWork && h->n_work_forced[near] <= kStepMaxForced;
+}
+
 bool one_launch(const btdf_t *h, bool near) {
-  return variant_has_step(h->variant) && h->nm() > 0 && h->nf == 1 && h->method != BTDF_FORCING_IMPLICIT &&
-         h->plane * h->prec < (1LL << 32) && h->n_work[near] > 0 && h->n_work[near] <= kStepMaxWork &&
-         h->n_work_forced[near] <= kStepMaxForced;
+  return h->nm() > 0 && h->nf == 1 && h->method != BTDF_FORCING_IMPLICIT && few_tiles(h, near);
 }
 
 int run_step(btdf_t *h, const LbmParams &p, const IbParams &ib, const void *A, void *B, bool near, hipStream_t s,
@@ -901,10 +925,25 @@ int run_step(btdf_t *h, const LbmParams &p, const IbParams &ib, const void *A, v
   k.reduce = run->pending;
   k.record = run->left == 1;
   k.count = 1;
-  HIPCHK(launch_step(h->prec, A, B, p, step_work(h, near), cur, k, s));
+  HIPCHK(launch_step(h->prec, true, A, B, p, step_work(h, near), cur, k, s));
   run->link = StepLink{cur.Fx, cur.Fy, word, 0, 0, 0};
   run->pending = true;
   run->left--;
+  return ok();
+}
+
+// The lattice part of a step whose marker forces are in the marker records:
+// the step kernel, or over many tiles the lattice kernel. (The marker kernels
+// left the ring entry in slot word 0; the counter goes by word 1.)
+static int lattice_step(btdf_t *h, const LbmParams &p, const IbParams &ib, const void *A, void *B, bool near,
+                        hipStream_t s) {
+  if (few_tiles(h, near)) {
+    HIPCHK(launch_step(h->prec, false, A, B, p, step_work(h, near), ib, StepLink{ib.Fx, ib.Fy, 1, 1, 0, 1}, s));
+    return ok();
+  }
+  const TileRange r = near ? TileRange{h->at<int>(h->off_fmap), h->n_groups(), h->n_near, 1}
+                           : TileRange{nullptr, 0, h->ntx * h->nty, 1};
+  HIPCHK(launch_lbm(h->prec, h->variant, A, B, p, r, ib, s));
   return ok();
 }
 
@@ -934,7 +973,10 @@ int finish_run(btdf_t *h, const IbParams &ib, hipStream_t s, StepRun *run) {
 int step_markers(btdf_t *h, const LbmParams &p, const IbParams &ib, const void *A, hipStream_t s, StepRun *run) {
   const int rc = flush_forces(ib, s, run);
   if (rc) return rc;
-  HIPCHK(launch_ib(h->prec, A, p, ib, s));
+  if (h->own_bodies)
+    HIPCHK(launch_body(h->prec, A, p, ib, s));
+  else
+    HIPCHK(launch_ib(h->prec, A, p, ib, s));
   run->left--;
   return ok();
 }
@@ -954,8 +996,8 @@ int enqueue_step(btdf_t *h, const LbmParams &p, const IbParams &ib, int src, hip
   if (te) HIPCHK(hipEventRecord(te->ib1, s));
   if (one) {
     if ((rc = run_step(h, p, ib, A, B, false, s, run))) return rc;
-  } else {
-    HIPCHK(launch_lbm(h->prec, h->variant, A, B, p, TileRange{nullptr, 0, h->ntx * h->nty, 1}, ib, s));
+  } else if ((rc = lattice_step(h, p, ib, A, B, false, s))) {
+    return rc;
   }
   if (te) HIPCHK(hipEventRecord(te->a1, s));
   // moving bodies advance after the step that used their positions, and after
@@ -1468,9 +1510,7 @@ static int near_markers(btdf_t *h, const LbmParams &p, const IbParams &ib, const
 static int near_step(btdf_t *h, const LbmParams &p, const IbParams &ib, const void *A, void *B, hipStream_t s,
                      StepRun *run) {
   if (one_launch(h, true)) return run_step(h, p, ib, A, B, true, s, run);
-  const TileRange r{h->at<int>(h->off_fmap), h->n_groups(), h->n_near, 1};
-  HIPCHK(launch_lbm(h->prec, h->variant, A, B, p, r, ib, s));
-  return ok();
+  return lattice_step(h, p, ib, A, B, true, s);
 }
 
 static int enqueue_pair(btdf_t *h, const LbmParams &p, const IbParams &ib, hipStream_t s, hipEvent_t *ev,

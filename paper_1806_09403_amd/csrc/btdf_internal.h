@@ -75,6 +75,7 @@ struct btdf_sim {
   std::vector<double> s_rkpm;              // RKPM: spreading factor ds epsilon_l per marker
   std::vector<double> bds;                 // arc length per marker of each body
   int max_body = 0;                        // markers of the largest body
+  bool own_bodies = false;                 // marker forces body by body (btdf_body.hip)
   std::string method_err;                  // set-up failure of the implicit / RKPM matrices
   // rigid motion (host mirror of the device integration): per body a moving
   // flag, angle, velocity and angular velocity, per marker its offset from

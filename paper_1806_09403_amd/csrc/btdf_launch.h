@@ -14,8 +14,15 @@ hipError_t launch_ib(int prec, const void *A, const LbmParams &p, const IbParams
 // a whole step A -> B over the tiles of w in one launch (direct forcing, one
 // pass), and the body forces of the step k names (btdf_step.hip)
 bool variant_has_step(int variant);
-hipError_t launch_step(int prec, const void *A, void *B, const LbmParams &p, const StepWork &w, const IbParams &ib,
-                       const StepLink &k, hipStream_t s);
+// (mark: the tiles form the marker forces; otherwise they read the marker
+// records, and k names this step's forces)
+hipError_t launch_step(int prec, bool mark, const void *A, void *B, const LbmParams &p, const StepWork &w,
+                       const IbParams &ib, const StepLink &k, hipStream_t s);
+// the marker forces of every body whose markers touch no other's, one
+// workgroup per body: the implicit method, or all forcing passes
+// (btdf_body.hip); bodies of at most kBodyMax markers
+constexpr int kBodyMax = 256;
+hipError_t launch_body(int prec, const void *A, const LbmParams &p, const IbParams &ib, hipStream_t s);
 hipError_t launch_step_flush(const IbParams &ib, const StepLink &k, hipStream_t s);
 hipError_t launch_rigid_move(const MoveParams &mp, const IbParams &ib, const StepLink &k, hipStream_t s);
 // two steps A -> C over the listed groups of width lattice tiles; with near

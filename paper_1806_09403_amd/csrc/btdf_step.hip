@@ -30,45 +30,6 @@ namespace {
 constexpr int kTX = 32, kTY = 8, kHalf = kTX * kTY;  // the tile; threads of half a workgroup
 constexpr int kMomX = kTX + 6, kMomY = kTY + 6;      // with the reach of a 4-point stencil around it
 
-// v of the lane that CTRL names (a data-parallel-primitive control word)
-template <int CTRL>
-__device__ __forceinline__ double dpp(double v) {
-  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, false);
-  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, false);
-  return __hiloint2double(hi, lo);
-}
-
-// Sum over the 16 lanes of a marker, in the order of a butterfly over lane
-// distances 8, 4, 2, 1 (row rotations by 8 and 4, then the quad permutations;
-// after the first, lanes 8 apart hold the same value, so a rotation by 4 is
-// the exchange with the lane 4 apart). Every lane ends with the sum.
-__device__ __forceinline__ double row_sum(double v) {
-  v += dpp<0x128>(v);
-  v += dpp<0x124>(v);
-  v += dpp<0x4E>(v);
-  v += dpp<0xB1>(v);
-  return v;
-}
-
-// rho and the unforced velocity u* (eqs 9-10, with G/2) of one node, from its
-// streamed deviations, whose first moment is m - u_ref
-template <typename T>
-__device__ __forceinline__ void node_moments(const T (&gq)[9], const LbmParams &p, double &rho, double &usx,
-                                             double &usy) {
-  double drho = 0.0, mx = 0.0, my = 0.0;
-#pragma unroll
-  for (int q = 0; q < 9; ++q) {
-    const double g = (double)gq[q];
-    drho += g;
-    mx += ex(q) * g;
-    my += ey(q) * g;
-  }
-  rho = 1.0 + drho;
-  const double inv = 1.0 / rho;
-  usx = (mx + p.urx + 0.5 * p.Gx) * inv;
-  usy = (my + p.ury + 0.5 * p.Gy) * inv;
-}
-
 // One chunk of a tile's markers: ids, stencil origins (wrapped; and relative
 // to the tile grown by the stencil's reach), delta weights (x then y),
 // velocity, spreading factor; then weight products and drs ds F_l in the
@@ -110,6 +71,38 @@ __device__ __forceinline__ void step_pulls(const T *__restrict__ A, const LbmPar
       else
         g[q] = load_global<T>(reinterpret_cast<const char *>(A + (long long)opp(q) * p.plane), row[1] + col[1]) + k[18 + q];
     }
+  }
+}
+
+// Stage a chunk of markers whose forces another kernel formed: weights,
+// drs ds F_l and origins from the marker records, ten threads per marker.
+template <typename T>
+__device__ __forceinline__ void stage_records(const LbmParams &p, int c0, int cnt, int tid, MarkerLds<T> &s_k) {
+  for (int k = tid; k < 16 * cnt; k += kHalf) {
+    const int e = k >> 4, w = k & 15;
+    const int l = ldg(p.tile_list, c0 + e);
+    const T *mw = reinterpret_cast<const T *>(p.mk_w) + 10 * (long long)l;
+    if (w < 8) s_k.w[e][w] = ldg(mw, w);
+    if (w == 8 || w == 9) s_k.F[e][w - 8] = ldg(mw, w);
+    if (w == 10) s_k.ix[e] = ldg(p.mk_ixy, 2 * l);
+    if (w == 11) s_k.iy[e] = ldg(p.mk_ixy, 2 * l + 1);
+  }
+}
+
+// The tile's nodes that the staged markers cover (bit e of s_mask), 16 lanes
+// per marker.
+template <typename T>
+__device__ __forceinline__ void mark_nodes(const LbmParams &p, int x0, int y0, int S, int cnt, int tid,
+                                           const MarkerLds<T> &s_k, unsigned long long (&s_mask)[kHalf]) {
+  const int a = tid & 3, c = (tid >> 2) & 3;
+  for (int e = tid >> 4; e < cnt; e += 2 * kHalf / 16) {
+    int sx = s_k.ix[e] + a, sy = s_k.iy[e] + c;
+    if (p.xper && sx >= p.nx) sx -= p.nx;
+    if (p.yper && sy >= p.ny) sy -= p.ny;
+    sx -= x0;
+    sy -= y0;
+    if (a < S && c < S && (unsigned)sx < (unsigned)kTX && (unsigned)sy < (unsigned)kTY)
+      atomicOr(&s_mask[sy * kTX + sx], 1ull << e);
   }
 }
 
@@ -246,7 +239,9 @@ __device__ __forceinline__ void spread_masked(const LbmParams &p, const MarkerLd
 
 }  // namespace
 
-template <typename T>
+// MARK: the tiles form their markers' forces; otherwise they are in the
+// marker records (other forcing methods, body_kernel or the marker kernel).
+template <typename T, bool MARK>
 __global__ __launch_bounds__(2 * kHalf) void step_kernel(const T *__restrict__ A, T *__restrict__ B, LbmParams p,
                                                          StepWork w, IbParams ib, StepLink k) {
   const int tid = (int)threadIdx.x, ht = tid & (kHalf - 1);
@@ -281,7 +276,7 @@ __global__ __launch_bounds__(2 * kHalf) void step_kernel(const T *__restrict__ A
     if (live) step_pulls<T>(A, p, x, y, g);
   } else {
     __shared__ MarkerLds<T> s_k;
-    __shared__ double s_m[3][kMomY][kMomX];
+    __shared__ double s_m[MARK ? 3 : 1][kMomY][kMomX];
     __shared__ unsigned long long s_mask[kHalf];
     const int S = stencil_size(p.kind), H = S - 1;
     // rho and u* at a node of the grown tile, given by its place there: nodes
@@ -295,57 +290,71 @@ __global__ __launch_bounds__(2 * kHalf) void step_kernel(const T *__restrict__ A
       return xw >= p.i0 && xw <= p.i1 && yw >= 0 && yw < p.ny;
     };
     auto put = [&](int i, int j, const T(&v)[9]) {
-      double r, u, t;
-      node_moments<T>(v, p, r, u, t);
-      s_m[0][j][i] = r;
-      s_m[1][j][i] = u;
-      s_m[2][j][i] = t;
+      if constexpr (MARK) {
+        double r, u, t;
+        node_moments<T>(v, p, r, u, t);
+        s_m[0][j][i] = r;
+        s_m[1][j][i] = u;
+        s_m[2][j][i] = t;
+      }
     };
-    if (!second) {
-      const int i = (ht & (kTX - 1)) + H, j = ht / kTX + H;
-      int xw, yw;
-      const bool in = place(i, j, xw, yw);
-      if (in) step_pulls<T>(A, p, xw, yw, g);
-      stage_markers<T>(p, ib, S, it.m0, min(kChunk, it.m1 - it.m0), ht, s_k);
-      if (in) put(i, j, g);
-    } else {
-      s_mask[ht] = 0;
-      // the ring of H nodes around the tile: H rows above and below, then the sides
-      const int W = kTX + 2 * H, n = 2 * H * (W + kTY);
-      // k / W for k < 2^9 and c / (2 H) for c < 48, by reciprocals
-      const int rw = H == 3 ? 1725 : (H == 2 ? 1821 : 1928), rh = H == 3 ? 10923 : (H == 2 ? 16384 : 32768);
-      for (int r = ht; r < n; r += kHalf) {
-        int i, j;
-        if (r < 2 * H * W) {
-          const int row = (r * rw) >> 16;
-          i = r - row * W;
-          j = row < H ? row : row + kTY;
-        } else {
-          const int e = r - 2 * H * W, row = (e * rh) >> 16, c = e - row * 2 * H;
-          i = c < H ? c : c + kTX;
-          j = H + row;
-        }
+    if constexpr (MARK) {
+      if (!second) {
+        const int i = (ht & (kTX - 1)) + H, j = ht / kTX + H;
         int xw, yw;
-        T v[9];
-        if (place(i, j, xw, yw)) {
-          step_pulls<T>(A, p, xw, yw, v);
-          put(i, j, v);
+        const bool in = place(i, j, xw, yw);
+        if (in) step_pulls<T>(A, p, xw, yw, g);
+        stage_markers<T>(p, ib, S, it.m0, min(kChunk, it.m1 - it.m0), ht, s_k);
+        if (in) put(i, j, g);
+      } else {
+        s_mask[ht] = 0;
+        // the ring of H nodes around the tile: H rows above and below, then the sides
+        const int W = kTX + 2 * H, n = 2 * H * (W + kTY);
+        // k / W for k < 2^9 and c / (2 H) for c < 48, by reciprocals
+        const int rw = H == 3 ? 1725 : (H == 2 ? 1821 : 1928), rh = H == 3 ? 10923 : (H == 2 ? 16384 : 32768);
+        for (int r = ht; r < n; r += kHalf) {
+          int i, j;
+          if (r < 2 * H * W) {
+            const int row = (r * rw) >> 16;
+            i = r - row * W;
+            j = row < H ? row : row + kTY;
+          } else {
+            const int e = r - 2 * H * W, row = (e * rh) >> 16, c = e - row * 2 * H;
+            i = c < H ? c : c + kTX;
+            j = H + row;
+          }
+          int xw, yw;
+          T v[9];
+          if (place(i, j, xw, yw)) {
+            step_pulls<T>(A, p, xw, yw, v);
+            put(i, j, v);
+          }
         }
       }
+    } else if (!second) {
+      if (live) step_pulls<T>(A, p, x, y, g);
+    } else {
+      s_mask[ht] = 0;
+      stage_records<T>(p, it.m0, min(kChunk, it.m1 - it.m0), ht, s_k);
     }
     __syncthreads();
     for (int c0 = it.m0;;) {
       const int cnt = min(kChunk, it.m1 - c0);
-      marker_forces<T>(p, ib, x0, y0, S, cnt, k.record != 0, tid, s_m, s_k, s_mask);
+      if constexpr (MARK)
+        marker_forces<T>(p, ib, x0, y0, S, cnt, k.record != 0, tid, s_m, s_k, s_mask);
+      else
+        mark_nodes<T>(p, x0, y0, S, cnt, tid, s_k, s_mask);
       __syncthreads();
       if (!second) spread_masked<T>(p, s_k, s_mask[ht], x, y, fibx, fiby);
       c0 += kChunk;
       if (c0 >= it.m1) break;
       __syncthreads();
-      if (!second)
-        stage_markers<T>(p, ib, S, c0, min(kChunk, it.m1 - c0), ht, s_k);
-      else
-        s_mask[ht] = 0;
+      if (second) s_mask[ht] = 0;
+      if constexpr (MARK) {
+        if (!second) stage_markers<T>(p, ib, S, c0, min(kChunk, it.m1 - c0), ht, s_k);
+      } else {
+        if (second) stage_records<T>(p, c0, min(kChunk, it.m1 - c0), ht, s_k);
+      }
       __syncthreads();
     }
   }
@@ -393,16 +402,20 @@ bool variant_has_step(int variant) {
   return variant == 6 && tx == kTX && ty == kTY;
 }
 
-hipError_t launch_step(int prec, const void *A, void *B, const LbmParams &p, const StepWork &w, const IbParams &ib,
-                       const StepLink &k, hipStream_t s) {
-  const int extra = k.count ? (k.reduce ? ib.nb : 0) + 1 : 0;
-  if (w.count + extra <= 0) return hipSuccess;
+template <typename T, bool MARK>
+static void launch_step_t(const void *A, void *B, const LbmParams &p, const StepWork &w, const IbParams &ib,
+                          const StepLink &k, int blocks, hipStream_t s) {
+  hipLaunchKernelGGL((step_kernel<T, MARK>), dim3(blocks), dim3(2 * kHalf), 0, s, (const T *)A, (T *)B, p, w, ib, k);
+}
+
+hipError_t launch_step(int prec, bool mark, const void *A, void *B, const LbmParams &p, const StepWork &w,
+                       const IbParams &ib, const StepLink &k, hipStream_t s) {
+  const int blocks = w.count + (k.count ? (k.reduce ? ib.nb : 0) + 1 : 0);
+  if (blocks <= 0) return hipSuccess;
   if (prec == 4)
-    hipLaunchKernelGGL(step_kernel<float>, dim3(w.count + extra), dim3(2 * kHalf), 0, s, (const float *)A, (float *)B,
-                       p, w, ib, k);
+    (mark ? launch_step_t<float, true> : launch_step_t<float, false>)(A, B, p, w, ib, k, blocks, s);
   else
-    hipLaunchKernelGGL(step_kernel<double>, dim3(w.count + extra), dim3(2 * kHalf), 0, s, (const double *)A,
-                       (double *)B, p, w, ib, k);
+    (mark ? launch_step_t<double, true> : launch_step_t<double, false>)(A, B, p, w, ib, k, blocks, s);
   return hipGetLastError();
 }
 

@@ -153,6 +153,45 @@ __device__ __forceinline__ void spread_gather(const int (&s_ix)[kChunk], const i
   }
 }
 
+// v of the lane that CTRL names (a data-parallel-primitive control word)
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+
+// Sum over the 16 lanes of a marker, in the order of a butterfly over lane
+// distances 8, 4, 2, 1 (row rotations by 8 and 4, then the quad permutations;
+// after the first, lanes 8 apart hold the same value, so a rotation by 4 is
+// the exchange with the lane 4 apart). Every lane ends with the sum.
+__device__ __forceinline__ double row_sum(double v) {
+  v += dpp<0x128>(v);
+  v += dpp<0x124>(v);
+  v += dpp<0x4E>(v);
+  v += dpp<0xB1>(v);
+  return v;
+}
+
+// rho and the unforced velocity u* (eqs 9-10, with G/2) of one node, from its
+// streamed deviations, whose first moment is m - u_ref
+template <typename T>
+__device__ __forceinline__ void node_moments(const T (&gq)[9], const LbmParams &p, double &rho, double &usx,
+                                             double &usy) {
+  double drho = 0.0, mx = 0.0, my = 0.0;
+#pragma unroll
+  for (int q = 0; q < 9; ++q) {
+    const double g = (double)gq[q];
+    drho += g;
+    mx += ex(q) * g;
+    my += ey(q) * g;
+  }
+  rho = 1.0 + drho;
+  const double inv = 1.0 / rho;
+  usx = (mx + p.urx + 0.5 * p.Gx) * inv;
+  usy = (my + p.ury + 0.5 * p.Gy) * inv;
+}
+
 // Convective outlet (d/dt + U d/dx = 0 on the ghost column, implicit upwind):
 // the ghost of B is (ghost of A + U column nx-2 of B) / (1 + U), written by
 // the lane that has just made column nx-2 (base: its offset, out: its
