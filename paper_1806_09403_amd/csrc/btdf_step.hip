@@ -16,7 +16,9 @@
 // A workgroup has eight waves. For a forced tile the first four take the
 // tile's nodes and stage the markers, the other four take the ring of nodes
 // around it, and all form forces; without markers the two halves take a tile
-// each. What a workgroup does is one 16-byte entry of a list made on the host
+// each. (A ninth wave for the 20 ring nodes past 256 of a 4-point stencil
+// gains 2% on the 200x120 channel but costs a fifth of the workgroups a CU
+// holds: 57.8 -> 67.3 us a step on 2560^2 with 200 cylinders.) What a workgroup does is one 16-byte entry of a list made on the host
 // (forced tiles first, as they take longest), so nothing is looked up on the
 // way to the first population load.
 #include "btdf_device.h"
@@ -26,9 +28,6 @@
 namespace btdf {
 
 namespace {
-
-constexpr int kTX = 32, kTY = 8, kHalf = kTX * kTY;  // the tile; threads of half a workgroup
-constexpr int kMomX = kTX + 6, kMomY = kTY + 6;      // with the reach of a 4-point stencil around it
 
 // One chunk of a tile's markers: ids, stencil origins (wrapped; and relative
 // to the tile grown by the stencil's reach), delta weights (x then y),
@@ -40,39 +39,6 @@ struct MarkerLds {
   T F[kChunk][2], w[kChunk][8];
   int l[kChunk], ix[kChunk], iy[kChunk];
 };
-
-// All pulls of node (x, y), in the grid, with the boundary readings of
-// pull(). Offsets within a plane are 32-bit: the columns and rows are wrapped
-// once for all directions (at a wall they stay in the grid, and a node next to
-// it replaces the three populations that came from beyond it).
-template <typename T>
-__device__ __forceinline__ void step_pulls(const T *__restrict__ A, const LbmParams &p, int x, int y, T (&g)[9]) {
-#pragma clang fp contract(off)
-  const unsigned pb = (unsigned)p.pitch * (unsigned)sizeof(T);
-  int xm = x - 1, xp = x + 1, ym = y - 1, yp = y + 1;
-  xm = xm < 0 ? (p.xper ? p.nx - 1 : 0) : xm;
-  xp = xp >= p.nx ? (p.xper ? 0 : p.nx - 1) : xp;
-  ym = ym < 0 ? (p.yper ? p.ny - 1 : 0) : ym;
-  yp = yp >= p.ny ? (p.yper ? 0 : p.ny - 1) : yp;
-  const unsigned row[3] = {(unsigned)ym * pb, (unsigned)y * pb, (unsigned)yp * pb};
-  const unsigned col[3] = {(unsigned)xm * (unsigned)sizeof(T), (unsigned)x * (unsigned)sizeof(T),
-                           (unsigned)xp * (unsigned)sizeof(T)};
-#pragma unroll
-  for (int q = 0; q < 9; ++q)
-    g[q] = load_global<T>(reinterpret_cast<const char *>(A + (long long)q * p.plane), row[1 - ey(q)] + col[1 - ex(q)]);
-  if (!p.yper && (y == 0 || y == p.ny - 1)) {
-    const __attribute__((address_space(4))) T *k = (const __attribute__((address_space(4))) T *)konst<T>(p);
-#pragma unroll
-    for (int q = 2; q < 9; ++q) {
-      if (ey(q) == 0 || y != (ey(q) > 0 ? 0 : p.ny - 1)) continue;
-      if (p.slip)
-        g[q] = load_global<T>(reinterpret_cast<const char *>(A + (long long)mir_y(q) * p.plane), row[1] + col[1 - ex(q)]) +
-               k[27 + q];
-      else
-        g[q] = load_global<T>(reinterpret_cast<const char *>(A + (long long)opp(q) * p.plane), row[1] + col[1]) + k[18 + q];
-    }
-  }
-}
 
 // Stage a chunk of markers whose forces another kernel formed: weights,
 // drs ds F_l and origins from the marker records, ten threads per marker.
@@ -95,7 +61,7 @@ template <typename T>
 __device__ __forceinline__ void mark_nodes(const LbmParams &p, int x0, int y0, int S, int cnt, int tid,
                                            const MarkerLds<T> &s_k, unsigned long long (&s_mask)[kHalf]) {
   const int a = tid & 3, c = (tid >> 2) & 3;
-  for (int e = tid >> 4; e < cnt; e += 2 * kHalf / 16) {
+  for (int e = tid >> 4; e < cnt; e += kBlock / 16) {
     int sx = s_k.ix[e] + a, sy = s_k.iy[e] + c;
     if (p.xper && sx >= p.nx) sx -= p.nx;
     if (p.yper && sy >= p.ny) sy -= p.ny;
@@ -143,7 +109,7 @@ __device__ __forceinline__ void marker_forces(const LbmParams &p, const IbParams
                                               bool record, int tid, const double (&s_m)[3][kMomY][kMomX],
                                               MarkerLds<T> &s_k, unsigned long long (&s_mask)[kHalf]) {
   const int node = tid & 15, a = node & 3, c = node >> 2, H = S - 1;
-  for (int e = tid >> 4; e - (tid >> 4) < cnt; e += 2 * kHalf / 16) {  // (whole waves: the sums need every lane)
+  for (int e = tid >> 4; e - (tid >> 4) < cnt; e += kBlock / 16) {  // (whole waves: the sums need every lane)
     const bool act = e < cnt;
     const int em = act ? e : 0;
     const int ix = s_k.ix[em], iy = s_k.iy[em];
@@ -242,10 +208,11 @@ __device__ __forceinline__ void spread_masked(const LbmParams &p, const MarkerLd
 // MARK: the tiles form their markers' forces; otherwise they are in the
 // marker records (other forcing methods, body_kernel or the marker kernel).
 template <typename T, bool MARK>
-__global__ __launch_bounds__(2 * kHalf) void step_kernel(const T *__restrict__ A, T *__restrict__ B, LbmParams p,
+__global__ __launch_bounds__(kBlock) void step_kernel(const T *__restrict__ A, T *__restrict__ B, LbmParams p,
                                                          StepWork w, IbParams ib, StepLink k) {
-  const int tid = (int)threadIdx.x, ht = tid & (kHalf - 1);
+  const int tid = (int)threadIdx.x;
   const bool second = tid >= kHalf;
+  const int ht = tid & (kHalf - 1);
   if ((int)blockIdx.x >= w.count) {  // workgroups past the tiles: the previous step's bodies, then the step counter
     const int gb = (int)blockIdx.x - w.count;
     if (second) return;
@@ -279,16 +246,7 @@ __global__ __launch_bounds__(2 * kHalf) void step_kernel(const T *__restrict__ A
     __shared__ double s_m[MARK ? 3 : 1][kMomY][kMomX];
     __shared__ unsigned long long s_mask[kHalf];
     const int S = stencil_size(p.kind), H = S - 1;
-    // rho and u* at a node of the grown tile, given by its place there: nodes
-    // past a periodic edge are taken at their images; nodes outside the fluid
-    // are left out (no stencil holds one)
-    auto place = [&](int i, int j, int &xw, int &yw) {
-      xw = x0 - H + i;
-      yw = y0 - H + j;
-      if (p.xper) xw = wrap_index(xw, p.nx);
-      if (p.yper) yw = wrap_index(yw, p.ny);
-      return xw >= p.i0 && xw <= p.i1 && yw >= 0 && yw < p.ny;
-    };
+    // rho and u* at a place of the tile grown by H
     auto put = [&](int i, int j, const T(&v)[9]) {
       if constexpr (MARK) {
         double r, u, t;
@@ -302,34 +260,24 @@ __global__ __launch_bounds__(2 * kHalf) void step_kernel(const T *__restrict__ A
       if (!second) {
         const int i = (ht & (kTX - 1)) + H, j = ht / kTX + H;
         int xw, yw;
-        const bool in = place(i, j, xw, yw);
+        const bool in = grid_place(p, x0, y0, H, i, j, xw, yw);
         if (in) step_pulls<T>(A, p, xw, yw, g);
         stage_markers<T>(p, ib, S, it.m0, min(kChunk, it.m1 - it.m0), ht, s_k);
         if (in) put(i, j, g);
       } else {
         s_mask[ht] = 0;
-        // the ring of H nodes around the tile: H rows above and below, then the sides
-        const int W = kTX + 2 * H, n = 2 * H * (W + kTY);
-        // k / W for k < 2^9 and c / (2 H) for c < 48, by reciprocals
-        const int rw = H == 3 ? 1725 : (H == 2 ? 1821 : 1928), rh = H == 3 ? 10923 : (H == 2 ? 16384 : 32768);
-        for (int r = ht; r < n; r += kHalf) {
-          int i, j;
-          if (r < 2 * H * W) {
-            const int row = (r * rw) >> 16;
-            i = r - row * W;
-            j = row < H ? row : row + kTY;
-          } else {
-            const int e = r - 2 * H * W, row = (e * rh) >> 16, c = e - row * 2 * H;
-            i = c < H ? c : c + kTX;
-            j = H + row;
-          }
-          int xw, yw;
-          T v[9];
-          if (place(i, j, xw, yw)) {
-            step_pulls<T>(A, p, xw, yw, v);
-            put(i, j, v);
-          }
-        }
+        // two turns at a 4-point stencil (the second of 20 nodes, in one
+        // wave): both turns' reads go out before the first is used
+        int i, j, i2, j2, xw, yw;
+        T v[9];
+        ring_place(ht, H, i, j);
+        const bool in = ht < ring_nodes(H) && grid_place(p, x0, y0, H, i, j, xw, yw);
+        if (in) step_pulls<T>(A, p, xw, yw, g);
+        ring_place(ht + kHalf, H, i2, j2);
+        const bool in2 = ht + kHalf < ring_nodes(H) && grid_place(p, x0, y0, H, i2, j2, xw, yw);
+        if (in2) step_pulls<T>(A, p, xw, yw, v);
+        if (in) put(i, j, g);
+        if (in2) put(i2, j2, v);
       }
     } else if (!second) {
       if (live) step_pulls<T>(A, p, x, y, g);
@@ -405,7 +353,7 @@ bool variant_has_step(int variant) {
 template <typename T, bool MARK>
 static void launch_step_t(const void *A, void *B, const LbmParams &p, const StepWork &w, const IbParams &ib,
                           const StepLink &k, int blocks, hipStream_t s) {
-  hipLaunchKernelGGL((step_kernel<T, MARK>), dim3(blocks), dim3(2 * kHalf), 0, s, (const T *)A, (T *)B, p, w, ib, k);
+  hipLaunchKernelGGL((step_kernel<T, MARK>), dim3(blocks), dim3(kBlock), 0, s, (const T *)A, (T *)B, p, w, ib, k);
 }
 
 hipError_t launch_step(int prec, bool mark, const void *A, void *B, const LbmParams &p, const StepWork &w,

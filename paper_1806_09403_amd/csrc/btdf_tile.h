@@ -339,4 +339,70 @@ __device__ __forceinline__ void lbm_tile(const T *__restrict__ A, T *__restrict_
   if (bad) p.flag[0] = -1;
 }
 
+// ---- the one-launch step: a tile and the ring around it
+constexpr int kTX = 32, kTY = 8, kHalf = kTX * kTY;  // the tile, and the threads that take its nodes
+constexpr int kBlock = 2 * kHalf;  // the workgroup: as many again for the ring
+constexpr int kMomX = kTX + 6, kMomY = kTY + 6;      // with the reach of a 4-point stencil around it
+
+// All pulls of node (x, y), in the grid, with the boundary readings of
+// pull(). Offsets within a plane are 32-bit: the columns and rows are wrapped
+// once for all directions (at a wall they stay in the grid, and a node next to
+// it replaces the three populations that came from beyond it).
+template <typename T>
+__device__ __forceinline__ void step_pulls(const T *__restrict__ A, const LbmParams &p, int x, int y, T (&g)[9]) {
+#pragma clang fp contract(off)
+  const unsigned pb = (unsigned)p.pitch * (unsigned)sizeof(T);
+  int xm = x - 1, xp = x + 1, ym = y - 1, yp = y + 1;
+  xm = xm < 0 ? (p.xper ? p.nx - 1 : 0) : xm;
+  xp = xp >= p.nx ? (p.xper ? 0 : p.nx - 1) : xp;
+  ym = ym < 0 ? (p.yper ? p.ny - 1 : 0) : ym;
+  yp = yp >= p.ny ? (p.yper ? 0 : p.ny - 1) : yp;
+  const unsigned row[3] = {(unsigned)ym * pb, (unsigned)y * pb, (unsigned)yp * pb};
+  const unsigned col[3] = {(unsigned)xm * (unsigned)sizeof(T), (unsigned)x * (unsigned)sizeof(T),
+                           (unsigned)xp * (unsigned)sizeof(T)};
+#pragma unroll
+  for (int q = 0; q < 9; ++q)
+    g[q] = load_global<T>(reinterpret_cast<const char *>(A + (long long)q * p.plane), row[1 - ey(q)] + col[1 - ex(q)]);
+  if (!p.yper && (y == 0 || y == p.ny - 1)) {
+    const __attribute__((address_space(4))) T *k = (const __attribute__((address_space(4))) T *)konst<T>(p);
+#pragma unroll
+    for (int q = 2; q < 9; ++q) {
+      if (ey(q) == 0 || y != (ey(q) > 0 ? 0 : p.ny - 1)) continue;
+      if (p.slip)
+        g[q] = load_global<T>(reinterpret_cast<const char *>(A + (long long)mir_y(q) * p.plane), row[1] + col[1 - ex(q)]) +
+               k[27 + q];
+      else
+        g[q] = load_global<T>(reinterpret_cast<const char *>(A + (long long)opp(q) * p.plane), row[1] + col[1]) + k[18 + q];
+    }
+  }
+}
+
+// The place of a ring node: k = 0 .. 2 H (kTX + 2 H + kTY) - 1 counts the H
+// rows below and above the tile, then the H columns on both sides (H = 1, 2, 3).
+__device__ __forceinline__ int ring_nodes(int H) { return 2 * H * (kTX + 2 * H + kTY); }
+__device__ __forceinline__ void ring_place(int k, int H, int &i, int &j) {
+  const int W = kTX + 2 * H;
+  // k / W for k < 2^9 and e / (2 H) for e < 48, by reciprocals
+  const int rw = H == 3 ? 1725 : (H == 2 ? 1821 : 1928), rh = H == 3 ? 10923 : (H == 2 ? 16384 : 32768);
+  if (k < 2 * H * W) {
+    const int row = (k * rw) >> 16;
+    i = k - row * W;
+    j = row < H ? row : row + kTY;
+  } else {
+    const int e = k - 2 * H * W, row = (e * rh) >> 16, c = e - row * 2 * H;
+    i = c < H ? c : c + kTX;
+    j = H + row;
+  }
+}
+
+// The grid node at place (i, j) of the tile (x0, y0) grown by H: past a
+// periodic edge its image; false outside the fluid.
+__device__ __forceinline__ bool grid_place(const LbmParams &p, int x0, int y0, int H, int i, int j, int &x, int &y) {
+  x = x0 - H + i;
+  y = y0 - H + j;
+  if (p.xper) x = wrap_index(x, p.nx);
+  if (p.yper) y = wrap_index(y, p.ny);
+  return x >= p.i0 && x <= p.i1 && y >= 0 && y < p.ny;
+}
+
 }  // namespace btdf
