@@ -14,7 +14,7 @@
 //   [ checkpoints or tape states | segment states | G x 2 | per-step marker
 //     records | marker adjoints and gradients | adjoint tile bins | tile sums |
 //     weights of the history (all, and one segment's) | control + one
-//     history slot | dJ/dA_0 in FP64 ]
+//     history slot | dJ/dA_0 in FP64 (the tile list until then) ]
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -44,6 +44,8 @@ struct AdjLayout {
   // adjoint tiles and their markers; markers covering each stencil node
   int ntx = 0, nty = 0;
   std::vector<int> toff, tlist, noff, nlist;
+  std::vector<int> tiles;  // the tiles that have markers, then the others
+  int n_forced = 0;
 };
 
 int64_t default_K(int64_t n) {
@@ -78,6 +80,12 @@ void adj_layout(const btdf_t *h, int64_t n, int64_t K, AdjLayout *L) {
   const int ntiles = L->ntx * L->nty;
   bin_markers(h, kAdjTX, kAdjTY, L->ntx, L->nty, L->toff, L->tlist);
   cover_lists(h, L->noff, L->nlist);
+  L->tiles.clear();
+  for (int forced = 1; forced >= 0; --forced) {
+    for (int t = 0; t < ntiles; ++t)
+      if ((L->toff[t + 1] > L->toff[t]) == (forced != 0)) L->tiles.push_back(t);
+    if (forced) L->n_forced = (int)L->tiles.size();
+  }
 
   const size_t M = (size_t)std::max(h->nm(), 1), B = (size_t)std::max(h->nb(), 1), d = sizeof(double);
   size_t o = 0;
@@ -181,9 +189,7 @@ int reverse_step(const Adj &X, const void *A, int64_t k, const double *hbar, int
   IbParams ik;
   X.slot_params(k, X.pa, X.iba, &pk, &ik);
   const AdjParams ak = X.adj_params(ik, hbar);
-  const int prec = X.h->prec;
-  HIPCHK(launch_adj_marker(prec, A, X.gbuf(gi), pk, ik, ak, s));
-  HIPCHK(launch_adj_lattice(prec, A, X.gbuf(gi), X.gbuf(gi ^ 1), pk, ak, s));
+  HIPCHK(launch_adj_step(X.h->prec, A, X.gbuf(gi), X.gbuf(gi ^ 1), pk, ik, ak, s));
   return ok();
 }
 
@@ -295,6 +301,7 @@ int adjoint_impl(btdf_t *h, int64_t n, int64_t K, const double *hist_bar, btdf_g
       (rc = put(s, w, L.off_tlist, L.tlist.data(), L.tlist.size() * sizeof(int))) ||
       (rc = put(s, w, L.off_noff, L.noff.data(), L.noff.size() * sizeof(int))) ||
       (rc = put(s, w, L.off_nlist, L.nlist.data(), L.nlist.size() * sizeof(int))) ||
+      (rc = put(s, w, L.off_out, L.tiles.data(), L.tiles.size() * sizeof(int))) ||
       (rc = put(s, w, L.off_hbar, hist_bar, (size_t)n * nb * 3 * d)))
     return rc;
   HIPCHK(hipMemsetAsync(w + L.off_xyb, 0, 2 * M * d, s));
@@ -325,6 +332,8 @@ int adjoint_impl(btdf_t *h, int64_t n, int64_t K, const double *hist_bar, btdf_g
   a.nty = L.nty;
   a.tile_off = reinterpret_cast<const int *>(w + L.off_toff);
   a.tile_list = reinterpret_cast<const int *>(w + L.off_tlist);
+  a.tiles = reinterpret_cast<const int *>(w + L.off_out);  // (its own use comes after the sweep)
+  a.n_forced = L.n_forced;
   a.node_off = reinterpret_cast<const int *>(w + L.off_noff);
   a.node_list = reinterpret_cast<const int *>(w + L.off_nlist);
   a.part = reinterpret_cast<double *>(w + L.off_part);

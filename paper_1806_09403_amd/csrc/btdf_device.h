@@ -331,6 +331,8 @@ constexpr int kAdjTX = 64, kAdjTY = 4;
 struct AdjParams {
   int ntx, nty;                     // adjoint tiles
   const int *tile_off, *tile_list;  // markers whose stencil touches each tile, ascending
+  const int *tiles;                 // the n_forced tiles that have any, then the others
+  int n_forced;
   // for each marker l and stencil lane k (16 per marker), the markers whose
   // stencil covers that node, ascending, packed as (marker << 4) | (dx << 2) | dy
   const int *node_off, *node_list;
