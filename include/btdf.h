@@ -217,8 +217,8 @@ int btdf_add_body(btdf_t *h, int n, const double *xy, const double *uv, double c
                   double ds, int *body_id);
 
 /* Replace the prescribed marker velocities of one body; uv: host [n][2].
- * Takes effect from the next enqueued step (synchronising). EINVAL for a
- * body that moves rigidly (its velocities follow the motion). */
+ * Takes effect from the next enqueued step; uv may be reused on return. EINVAL
+ * for a body that moves rigidly (its velocities follow the motion). */
 int btdf_set_marker_velocity(btdf_t *h, int body, const double *uv);
 
 /* Rigid motion of one body from the next step on (eq 4 for a rigid body
@@ -254,7 +254,8 @@ int btdf_step(btdf_t *h, int64_t n);
 
 /* Same as btdf_step, but times the kernels with HIP events on the handle's
  * stream and writes, in milliseconds per step, the duration of the marker
- * kernel (*ms_ib, 0 if no bodies) and of the lattice launches (*ms_lbm).
+ * kernel (*ms_ib, 0 if no bodies, or where a step is one launch that forms
+ * the forces itself) and of the lattice launches (*ms_lbm).
  * The events are created on the first timed call and kept until
  * btdf_destroy. Synchronising. */
 int btdf_step_timed(btdf_t *h, int64_t n, double *ms_ib, double *ms_lbm);
