@@ -208,7 +208,7 @@ int recompute_segment(const Adj &X, int set, int64_t len, hipStream_t s) {
     if (k + 1 == len) break;
     if (one)
       HIPCHK(launch_step(prec, true, X.seg(set, k), X.seg(set, k + 1), pk, step_work(X.h, false), ik,
-                         StepLink{nullptr, nullptr, 0, 0, 1, 0}, s));
+                         StepLink{nullptr, nullptr, 0, 0, 1, 0}, MoveParams{}, s));
     else
       HIPCHK(launch_lbm(prec, X.h->variant, X.seg(set, k), X.seg(set, k + 1), pk, all, ik, s));
   }
@@ -371,7 +371,7 @@ int adjoint_impl(btdf_t *h, int64_t n, int64_t K, const double *hist_bar, btdf_g
       const TileRange all{nullptr, 0, X.nt, 1};
       if (one_launch(h, false)) {
         link.word = (int)(t & 1);
-        HIPCHK(launch_step(prec, true, A_of(t), B, pt, step_work(h, false), it, link, s));
+        HIPCHK(launch_step(prec, true, A_of(t), B, pt, step_work(h, false), it, link, MoveParams{}, s));
         link = StepLink{it.Fx, it.Fy, 0, 1, 1, 1};
       } else {
         HIPCHK(launch_ib(prec, A_of(t), pt, it, s));
@@ -380,7 +380,7 @@ int adjoint_impl(btdf_t *h, int64_t n, int64_t K, const double *hist_bar, btdf_g
     }
     if (one_launch(h, false)) {
       link.word = (int)((n - 1) & 1);
-      HIPCHK(launch_step_flush(X.ib, link, s));
+      HIPCHK(launch_step_flush(X.ib, link, MoveParams{}, s));
     }
     h->cur = 1 - cur0;
     h->steps += n;

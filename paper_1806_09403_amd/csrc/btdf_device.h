@@ -273,15 +273,20 @@ struct MarkerUv {
 };
 
 // rigid body motion, one workgroup per body after each step
+// One set of the bodies' places: [nb][4] theta, vx, vy, omega; centres;
+// markers and their velocities.
+struct BodyPlaces {
+  double *state, *cx, *cy, *X, *Y, *U, *V;
+};
+// The rigid motion of one step, from the places the step uses to those of the
+// next (the same set, or in one-launch steps the other of two).
 struct MoveParams {
-  int nb;
+  int nb;                  // 0: no body moves
+  int copy;                // 1: the places as they are, no motion
   const int *body_off;
-  const int *moving;   // [nb]
-  double *state;       // [nb][4]: theta, vx, vy, omega
-  double *cx, *cy;     // body centres
-  double *X, *Y, *U, *V;
-  const double *rxy;   // [nm][2]: offset from the centre at angle 0
-  int reduce;          // 1: sum the step's body forces first (one-launch steps)
+  const int *moving;       // [nb]
+  const double *rxy;       // [nm][2]: offset from the centre at angle 0
+  BodyPlaces from, to;
 };
 
 struct IbParams {

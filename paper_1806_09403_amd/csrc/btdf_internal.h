@@ -130,7 +130,7 @@ struct btdf_sim {
   int pitch = 0;
   long long plane = 0;
   size_t off_pop[2] = {0, 0}, off_ctl = 0, grid_bytes = 0;
-  size_t off_hist = 0, off_mk = 0, off_mkalt = 0, off_mkw = 0, off_mkixy = 0, off_mkbody = 0, off_body = 0, off_boff = 0,
+  size_t off_hist = 0, off_mk = 0, off_mkalt = 0, off_places = 0, off_mkw = 0, off_mkixy = 0, off_mkbody = 0, off_body = 0, off_boff = 0,
          off_toff = 0, off_tlist = 0, off_tmap = 0, off_coff = 0, off_clist = 0, off_mdfc = 0, off_mdff = 0,
          off_moff = 0, off_minv = 0, off_motion = 0, off_rxy = 0, off_fmap = 0, off_rwin = 0, off_near = 0, off_work = 0, off_pop3 = 0, off_pop4 = 0, off_pop5 = 0, off_pop6 = 0, total = 0;
   bool layout_ok = false;  // host layout current for bodies and tiles
@@ -253,6 +253,7 @@ struct StepRun {
   bool pending = false;    // the last one's body forces are not summed yet
   bool side = false;       // a pass's large groups are on the second stream (join_ev ends them)
   StepLink link{};
+  int places = 0;          // moving bodies: which of the two sets of places the next one-launch step uses
 };
 // Whether a step takes one launch, over all tiles or (near) over the blocked
 // pass's near tiles.

@@ -17,14 +17,14 @@ bool variant_has_step(int variant);
 // (mark: the tiles form the marker forces; otherwise they read the marker
 // records, and k names this step's forces)
 hipError_t launch_step(int prec, bool mark, const void *A, void *B, const LbmParams &p, const StepWork &w,
-                       const IbParams &ib, const StepLink &k, hipStream_t s);
+                       const IbParams &ib, const StepLink &k, const MoveParams &mp, hipStream_t s);
 // the marker forces of every body whose markers touch no other's, one
 // workgroup per body: the implicit method, or all forcing passes
 // (btdf_body.hip); bodies of at most kBodyMax markers
 constexpr int kBodyMax = 256;
 hipError_t launch_body(int prec, const void *A, const LbmParams &p, const IbParams &ib, hipStream_t s);
-hipError_t launch_step_flush(const IbParams &ib, const StepLink &k, hipStream_t s);
-hipError_t launch_rigid_move(const MoveParams &mp, const IbParams &ib, const StepLink &k, hipStream_t s);
+hipError_t launch_step_flush(const IbParams &ib, const StepLink &k, const MoveParams &mp, hipStream_t s);
+hipError_t launch_rigid_move(const MoveParams &mp, hipStream_t s);
 // two steps A -> C over the listed groups of width lattice tiles; with near
 // non-null, edge nodes next to a near tile also store their first step in X
 hipError_t launch_lbm2(int prec, int variant, int width, const void *A, void *C, const LbmParams &p, const int *map,

@@ -11,7 +11,8 @@
 // values in the same order, so all use the same bits, which are those of the
 // marker kernel; the tile that holds its stencil origin stores F_l. The body
 // forces (eq 27) need every F_l of the step: the next step's launch sums
-// them, or step_flush_kernel after the last step.
+// them, or step_flush_kernel after the last step. The same workgroups place
+// rigidly moving bodies for the step after, in the other of two sets of places.
 //
 // A workgroup has eight waves. For a forced tile the first four take the
 // tile's nodes and stage the markers, the other four take the ring of nodes
@@ -205,18 +206,28 @@ __device__ __forceinline__ void spread_masked(const LbmParams &p, const MarkerLd
 
 }  // namespace
 
+// What a launch with moving bodies has on top (the others are spared the
+// arguments: 0.1 us a launch).
+template <bool MOVE>
+struct Motion {};
+template <>
+struct Motion<true> {
+  MoveParams mp;
+};
+
 // MARK: the tiles form their markers' forces; otherwise they are in the
 // marker records (other forcing methods, body_kernel or the marker kernel).
-template <typename T, bool MARK>
+// MOVE: the bodies' workgroups also place them for the next step.
+template <typename T, bool MARK, bool MOVE>
 __global__ __launch_bounds__(kBlock) void step_kernel(const T *__restrict__ A, T *__restrict__ B, LbmParams p,
-                                                         StepWork w, IbParams ib, StepLink k) {
+                                                         StepWork w, IbParams ib, StepLink k, Motion<MOVE> motion) {
   const int tid = (int)threadIdx.x;
   const bool second = tid >= kHalf;
   const int ht = tid & (kHalf - 1);
   if ((int)blockIdx.x >= w.count) {  // workgroups past the tiles: the previous step's bodies, then the step counter
     const int gb = (int)blockIdx.x - w.count;
     if (second) return;
-    if (gb >= (k.reduce ? ib.nb : 0)) {
+    if (gb >= (k.reduce || MOVE ? ib.nb : 0)) {
       if (tid == 0) {
         const long long n = p.step_ctr[0];
         ib.slot[k.word] = (int)(n % ib.hist_cap);
@@ -224,8 +235,23 @@ __global__ __launch_bounds__(kBlock) void step_kernel(const T *__restrict__ A, T
       }
       return;
     }
+    // (moving bodies: the previous step's places are those the next step's
+    // take the room of)
     __shared__ double red[3][kHalf / 64];
-    body_reduce<kHalf>(ib, k.Fx, k.Fy, ib.slot[k.word ^ 1], gb, tid, red);
+    if (k.reduce) {
+      IbParams last = ib;
+      if constexpr (MOVE) {
+        last.X = motion.mp.to.X;
+        last.Y = motion.mp.to.Y;
+        last.cx = motion.mp.to.cx;
+        last.cy = motion.mp.to.cy;
+      }
+      body_reduce<kHalf>(last, k.Fx, k.Fy, ib.slot[k.word ^ 1], gb, tid, red);
+    }
+    if constexpr (MOVE) {
+      __syncthreads();
+      move_body<kHalf>(motion.mp, gb, tid);
+    }
     return;
   }
   // (made on the host and never written on the device: constant memory, one scalar load)
@@ -338,9 +364,13 @@ __global__ __launch_bounds__(kBlock) void step_kernel(const T *__restrict__ A, T
 }
 
 // the body forces of the step whose marker forces are in k (one workgroup per body)
-__global__ __launch_bounds__(kHalf) void step_flush_kernel(IbParams ib, StepLink k) {
+__global__ __launch_bounds__(kHalf) void step_flush_kernel(IbParams ib, StepLink k, MoveParams mp) {
   __shared__ double red[3][kHalf / 64];
   body_reduce<kHalf>(ib, k.Fx, k.Fy, ib.slot[k.word], (int)blockIdx.x, (int)threadIdx.x, red);
+  if (mp.nb) {
+    __syncthreads();
+    move_body<kHalf>(mp, (int)blockIdx.x, (int)threadIdx.x);
+  }
 }
 
 // whether a launch shape's tiles are those of the one-launch step
@@ -350,26 +380,37 @@ bool variant_has_step(int variant) {
   return variant == 6 && tx == kTX && ty == kTY;
 }
 
-template <typename T, bool MARK>
+template <typename T, bool MARK, bool MOVE>
 static void launch_step_t(const void *A, void *B, const LbmParams &p, const StepWork &w, const IbParams &ib,
-                          const StepLink &k, int blocks, hipStream_t s) {
-  hipLaunchKernelGGL((step_kernel<T, MARK>), dim3(blocks), dim3(kBlock), 0, s, (const T *)A, (T *)B, p, w, ib, k);
+                          const StepLink &k, const Motion<MOVE> &motion, int blocks, hipStream_t s) {
+  hipLaunchKernelGGL((step_kernel<T, MARK, MOVE>), dim3(blocks), dim3(kBlock), 0, s, (const T *)A, (T *)B, p, w, ib,
+                     k, motion);
+}
+template <typename T>
+static void launch_step_p(bool mark, const void *A, void *B, const LbmParams &p, const StepWork &w,
+                          const IbParams &ib, const StepLink &k, const MoveParams &mp, int blocks, hipStream_t s) {
+  if (mp.nb)  // (only steps that form the marker forces have moving bodies)
+    launch_step_t<T, true, true>(A, B, p, w, ib, k, Motion<true>{mp}, blocks, s);
+  else if (mark)
+    launch_step_t<T, true, false>(A, B, p, w, ib, k, Motion<false>{}, blocks, s);
+  else
+    launch_step_t<T, false, false>(A, B, p, w, ib, k, Motion<false>{}, blocks, s);
 }
 
 hipError_t launch_step(int prec, bool mark, const void *A, void *B, const LbmParams &p, const StepWork &w,
-                       const IbParams &ib, const StepLink &k, hipStream_t s) {
-  const int blocks = w.count + (k.count ? (k.reduce ? ib.nb : 0) + 1 : 0);
+                       const IbParams &ib, const StepLink &k, const MoveParams &mp, hipStream_t s) {
+  const int blocks = w.count + (k.count ? (k.reduce || mp.nb ? ib.nb : 0) + 1 : 0);
   if (blocks <= 0) return hipSuccess;
   if (prec == 4)
-    (mark ? launch_step_t<float, true> : launch_step_t<float, false>)(A, B, p, w, ib, k, blocks, s);
+    launch_step_p<float>(mark, A, B, p, w, ib, k, mp, blocks, s);
   else
-    (mark ? launch_step_t<double, true> : launch_step_t<double, false>)(A, B, p, w, ib, k, blocks, s);
+    launch_step_p<double>(mark, A, B, p, w, ib, k, mp, blocks, s);
   return hipGetLastError();
 }
 
-hipError_t launch_step_flush(const IbParams &ib, const StepLink &k, hipStream_t s) {
+hipError_t launch_step_flush(const IbParams &ib, const StepLink &k, const MoveParams &mp, hipStream_t s) {
   if (ib.nb <= 0) return hipSuccess;
-  hipLaunchKernelGGL(step_flush_kernel, dim3(ib.nb), dim3(kHalf), 0, s, ib, k);
+  hipLaunchKernelGGL(step_flush_kernel, dim3(ib.nb), dim3(kHalf), 0, s, ib, k, mp);
   return hipGetLastError();
 }
 

@@ -57,6 +57,49 @@ __device__ void body_reduce(const IbParams &ib, const double *Fl_x, const double
   }
 }
 
+// Body b's places one step on, by one workgroup of NT threads: the centre and
+// angle advance, the markers sit at c + R(theta) r with the rigid velocity.
+template <int NT>
+__device__ __forceinline__ void move_body(const MoveParams &mp, int b, int tid) {
+#pragma clang fp contract(off)
+  const double *st = mp.from.state + 4 * (long long)b;
+  const bool moves = mp.moving[b] && !mp.copy;
+  const double vx = st[1], vy = st[2], om = st[3];
+  const double cx = moves ? mp.from.cx[b] + vx : mp.from.cx[b];
+  const double cy = moves ? mp.from.cy[b] + vy : mp.from.cy[b];
+  const double th = moves ? st[0] + om : st[0];
+  const int l0 = mp.body_off[b], l1 = mp.body_off[b + 1];
+  __syncthreads();  // every lane has read the old state
+  if (tid == 0) {
+    double *to = mp.to.state + 4 * (long long)b;
+    mp.to.cx[b] = cx;
+    mp.to.cy[b] = cy;
+    to[0] = th;
+    to[1] = vx;
+    to[2] = vy;
+    to[3] = om;
+  }
+  if (!moves) {
+    for (int l = l0 + tid; l < l1; l += NT) {
+      mp.to.X[l] = mp.from.X[l];
+      mp.to.Y[l] = mp.from.Y[l];
+      mp.to.U[l] = mp.from.U[l];
+      mp.to.V[l] = mp.from.V[l];
+    }
+    return;
+  }
+  const double c = cos(th), s = sin(th);
+  for (int l = l0 + tid; l < l1; l += NT) {
+    const double rx = mp.rxy[2 * (long long)l], ry = mp.rxy[2 * (long long)l + 1];
+    const double X = cx + c * rx - s * ry;
+    const double Y = cy + s * rx + c * ry;
+    mp.to.X[l] = X;
+    mp.to.Y[l] = Y;
+    mp.to.U[l] = vx - om * (Y - cy);
+    mp.to.V[l] = vy + om * (X - cx);
+  }
+}
+
 constexpr int kChunk = 64;  // markers staged in LDS per pass
 
 template <typename T, bool NT>

@@ -153,6 +153,33 @@ def test_passes_of_bodies_near_each_other_match_the_oracle(gap):
     g.close()
 
 
+@pytest.mark.parametrize("precision", [4, 8])
+@pytest.mark.parametrize("bc", [W.FULLY_PERIODIC, WALLS_Y])
+def test_moving_bodies_in_one_and_two_launches_are_the_same_bits(bc, precision):
+    """A one-launch step leaves the next step's places in the second of two
+    sets: odd and even runs, past a rebuild of the tile lists, beside a body at
+    rest whose velocities change between runs, in graphs and timed."""
+    c = case(35, 90, 61, W.COS4, bc, [(0.3, 0.5, 12.0, 40), (0.7, 0.45, 9.0, 300), (0.55, 0.7, 5.0, 16)])
+    uv = np.random.default_rng(7).uniform(-0.01, 0.01, (300, 2))
+
+    def run(timed=False, **options):
+        s = gpu_of(c, precision, **options)
+        s.set_body_motion(0, 0.02, 0.011, 0.004)
+        s.set_body_motion(2, -0.013, 0.004, -0.006)
+        for k, n in enumerate((1, 2, 1, 7, 60)):
+            s.step_timed(n) if timed else s.step(n)
+            if k == 2:
+                s.set_marker_velocity(1, uv)
+        r = dict(results(s, 71), xy=s.marker_positions(), states=np.array([s.body_state(b) for b in range(3)]))
+        s.close()
+        return r
+
+    want = run(LBM_VARIANT=0)
+    for chunk in (0, 4, 5):
+        same(run(LBM_VARIANT=6, GRAPH_CHUNK=chunk), want)
+    same(run(timed=True, LBM_VARIANT=6), want)
+
+
 @pytest.mark.parametrize("precision,depth", [(4, 5), (4, 4), (8, 3)])
 @pytest.mark.parametrize("bc", [W.FULLY_PERIODIC, W.FAR_FIELD, INLET])
 def test_passes_beside_the_near_tiles_are_the_same_bits(bc, precision, depth):
