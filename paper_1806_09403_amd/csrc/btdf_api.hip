@@ -198,16 +198,22 @@ static bool has_group(const btdf_t *h, int d, int code) {
 // The shapes of the launches of a pass of depth d, level by level (tiles
 // are packed into the first level's groups, the rest into the next
 // level's): groups of four tiles along rows, then two, then single tiles.
-// (The launch shape decides which of them have a pass; d is kept for
-// shapes that only one depth has.)
+// (The launch shape decides which of them have a pass.)
 void group_kinds(int variant, int prec, int d, int kind[kLevels]) {
   (void)variant;
-  (void)prec;
   // five steps: squares of two by two tiles first (the fewest recomputed
   // halo nodes per node), then columns of two, rows of two, single tiles
   static const int rows[kLevels] = {kGroup4x1, kGroup1x4, kGroup2x1, kGroup1x1};
   static const int squares[kLevels] = {kGroup2x2, kGroup1x2, kGroup2x1, kGroup1x1};
-  for (int i = 0; i < kLevels; ++i) kind[i] = d >= 5 ? squares[i] : rows[i];
+  // Three steps in FP64: a row of four takes 114 KB of LDS, so that a CU holds
+  // one workgroup whose loads and collisions take turns; rows of two leave room
+  // for two. Per step, rows of four / two: 2048^2 58.1 / 53.5 us (with 125
+  // cylinders 70.0 / 60.7), 3072^2 with 280 154 / 143, 4096^2 with 500 257 /
+  // 234, 6144x4096 345 / 303, 1200x1000 equal at 23.3; in FP32 (57 KB and 29)
+  // 37.5 / 39.1 on 2048^2 and 115.4 / 116.0 on 4096^2.
+  static const int pairs[kLevels] = {kGroup2x1, kGroup1x4, kGroup1x1, kNoGroup};
+  const int *k = d >= 5 ? squares : (d == 3 && prec == 8 ? pairs : rows);
+  for (int i = 0; i < kLevels; ++i) kind[i] = k[i];
 }
 
 // Whether the pass's large groups run on a second stream beside the near
