@@ -309,3 +309,28 @@ def test_reversed_steps_match_the_oracle(seed, nx, ny, kind, bc, bodies, n):
         scale = np.max(np.abs(ref), initial=0.0)
         assert np.max(np.abs(got - ref), initial=0.0) <= 1e-11 * scale + 1e-300, gk
     s.close()
+
+
+@pytest.mark.parametrize("precision", [4, 8])
+def test_reversed_steps_of_a_lattice_of_many_tiles(precision):
+    """Above 28 000 tiles those no stencil touches have launches of their own.
+    A strip of 64 x 112 400 nodes (28 100 tiles) at rest but for a body: within
+    its reach the gradients are those of a strip of 64 x 64, beyond it zero."""
+    from paper_1806_09403_amd import Sim
+    n = 3
+    rng = np.random.default_rng(81)
+    uv, hbar = rng.uniform(-0.02, 0.02, (25, 2)), rng.standard_normal((n, 1, 3))
+    b = W.cylinder_body(30.3, 31.7, 8.0, 25)
+    grads = []
+    for ny in (64, 112400):
+        s = Sim(64, ny, 0.8, W.COS4, 2.6, W.FULLY_PERIODIC, init=(1.0, 0.02, 0.01), precision=precision)
+        s.add_body(b.xy, uv, b.cx, b.cy, b.ds)
+        g, _ = s.adjoint(n, hbar)
+        s.close()
+        grads.append(g)
+    small, large = grads
+    assert np.any(small["populations"])
+    assert np.array_equal(large["populations"][:, :64], small["populations"])
+    assert not np.any(large["populations"][:, 64:])
+    for k in ("body_force", "marker_xy", "marker_uv", "centres"):
+        assert np.array_equal(large[k], small[k]), k
