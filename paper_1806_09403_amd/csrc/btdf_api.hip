@@ -483,9 +483,10 @@ bool bodies_apart(btdf_t *h) {
 }
 
 // The work lists of one-launch steps: the tiles with markers one per entry,
-// then the others two per entry, over all tiles and over the near tiles. None
-// for launch shapes that have no such step.
-void step_items(btdf_t *h) {
+// then the others two per entry, over all tiles (filled up with empty entries
+// to least) and over the near tiles. None for launch shapes that have no such
+// step.
+void step_items(btdf_t *h, int least) {
   h->work.clear();
   h->n_work[0] = h->n_work[1] = h->n_work_forced[0] = h->n_work_forced[1] = 0;
   if (!variant_has_step(h->variant) || h->owner || h->ntx > 0xffff || h->nty > 0x7fff) return;
@@ -509,6 +510,7 @@ void step_items(btdf_t *h) {
         h->work.push_back({code(t), -1, 0, 0});
       half = !half;
     }
+    if (!near && h->work.size() < (size_t)least) h->work.resize(least, StepItem{-1, -1, 0, 0});
     h->n_work[near] = (int)(h->work.size() - start);
   }
 }
@@ -611,7 +613,7 @@ void compute_layout(btdf_t *h) {
   h->off_near = o;  // one flag per tile
   o = align256(o + (size_t)max_tiles);
   h->off_work = o;  // one-launch steps: over all tiles and over the near tiles
-  step_items(h);
+  step_items(h, 0);
   o = align256(o + (h->owner ? 0 : 2 * (size_t)max_tiles * sizeof(StepItem)));
   h->off_pop3 = o;  // the near tiles' intermediate states n+1 .. n+depth-1
   o = align256(o + (h->depth >= 2 || h->reserve_pass ? pop_bytes : 0));
@@ -1473,7 +1475,14 @@ static int rebin(btdf_t *h) {
   int rc;
   if ((rc = upload(h, h->off_toff, h->tile_off.data(), h->tile_off.size() * sizeof(int)))) return rc;
   if ((rc = upload(h, h->off_tlist, h->tile_list.data(), h->tile_list.size() * sizeof(int)))) return rc;
-  step_items(h);
+  // A graph holds the length of the list and which launches take it: as tiles
+  // gain and lose markers the list keeps its greatest length so far, filled up
+  // with entries without a tile, and where it grows or the launches change the
+  // graph is dropped. (A tile is in the list once, so it fits its region.)
+  const int len = h->n_work[0];
+  const bool few = few_tiles(h, false), one = one_launch(h, false);
+  step_items(h, len);
+  if (h->n_work[0] != len || few_tiles(h, false) != few || one_launch(h, false) != one) drop_graph(h);
   if ((rc = upload(h, h->off_work, h->work.data(), h->work.size() * sizeof(StepItem)))) return rc;
   if ((rc = upload(h, h->off_tmap, h->tile_map.data(), h->tile_map.size() * sizeof(int)))) return rc;
   HIPCHK(hipStreamSynchronize(h->stream));

@@ -255,8 +255,8 @@ struct StepLink {
   int count;              // 1: advance the step counter
 };
 // What one workgroup of the one-launch step does: a tile with the markers
-// m0 .. m1 of the tile list, or two tiles without markers (t1 = -1: one).
-// Tiles as tile column | tile row << 16.
+// m0 .. m1 of the tile list, or two tiles without markers (t1 = -1: one; both
+// -1: none). Tiles as tile column | tile row << 16.
 struct alignas(16) StepItem {
   int t0, t1, m0, m1;
 };

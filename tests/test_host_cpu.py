@@ -1,0 +1,73 @@
+"""What the host side enqueues, without a GPU: libbtdf runs in a child process
+over a stand-in for the HIP runtime (host_hip.c) whose kernels do nothing and
+which looks over every launch of the one-launch step where it would run. Each
+such launch has to step every tile of the lattice exactly once."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PRELUDE = """
+import ctypes
+import numpy as np
+import btdf_workloads as W
+from paper_1806_09403_amd import _lib, api
+hip = ctypes.CDLL(None)
+
+def handle(nx, ny, bodies, precision=8):
+    h = api.btdf_create(nx, ny, 0.8, W.COS4, 2.6, W.FULLY_PERIODIC, precision=precision)
+    for b in bodies:
+        api.btdf_add_body(h, b.xy, None, b.cx, b.cy, b.ds)
+    return h
+
+def steps_found():
+    p = ctypes.POINTER(ctypes.c_int)()
+    n = hip.host_hip_steps(ctypes.byref(p))
+    return np.ctypeslib.as_array(p, (n, 4)).copy() if n else np.zeros((0, 4), int)
+"""
+
+
+@pytest.fixture(scope="module")
+def stand_in(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("hip") / "libhost_hip.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-Wall", os.path.join(ROOT, "tests", "host_hip.c"), "-o", out,
+                    "-ldl"], check=True)
+    return out
+
+
+def child(stand_in, code):
+    env = dict(os.environ)
+    env["LD_PRELOAD"] = " ".join([stand_in] + env.get("LD_PRELOAD", "").split())
+    r = subprocess.run([sys.executable, "-c", PRELUDE + code], cwd=ROOT, env=env, capture_output=True, text=True,
+                       timeout=600)
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-4000:]
+    return r.stdout
+
+
+@pytest.mark.parametrize("velocity", [(0.02, 0.01, 0.0), (0.0, 0.02, 0.0), (-0.015, 0.0, 0.001)])
+def test_every_step_of_moving_bodies_covers_every_tile(stand_in, velocity):
+    """The work list of a step changes its length as bodies move from tile to
+    tile; steps enqueued singly and steps replayed from a graph both take the
+    whole list of the moment."""
+    child(stand_in, """
+tiles = 10 * 25
+for chunk in (0, 8, 5, 50):
+    before = len(steps_found())
+    h = handle(300, 200, [W.cylinder_body(90.0, 100.0, 12.0, 38)])
+    api.btdf_set_option(h, _lib.OPT_GRAPH_CHUNK, chunk)
+    api.btdf_set_body_motion(h, 0, *%r)
+    forced = set()
+    for k in range(60):
+        api.btdf_step(h, 17)
+        forced.add(api.btdf_get_option(h, _lib.OPT_FORCED_TILES))
+    f = steps_found()[before:]
+    assert len(forced) > 1, forced                       # (the case keeps its purpose)
+    assert len(f) == 60 * 17, len(f)
+    bad = np.flatnonzero((f[:, 2] != tiles) | (f[:, 3] != 0))
+    assert bad.size == 0, (chunk, bad[:5], f[bad[:5]])
+    assert np.all(f[:, 1] > f[:, 0])
+    api.btdf_destroy(h)
+""" % (velocity,))
