@@ -880,15 +880,19 @@ static int read_forces(btdf_t *h, int64_t first, int64_t cnt, double *out) {
   const int row = 3 * h->nb();
   const size_t bytes = (size_t)cnt * row * sizeof(double), need = bytes + sizeof(double);
   const double *hist = h->at<double>(h->off_hist);
-  if (need <= kReportBytes && ++h->reports > 1) {
-    if (h->pin_bytes < need) {
-      if (h->pin) HIPCHK(hipHostFree(h->pin));
-      h->pin = nullptr;
-      h->pin_bytes = 0;
-      const size_t cap = (need + 4095) / 4096 * 4096;
-      HIPCHK(hipHostMalloc((void **)&h->pin, cap, hipHostMallocDefault));
+  if (need <= kReportBytes && ++h->reports > 1 && h->pin_bytes < need) {
+    if (h->pin) HIPCHK(hipHostFree(h->pin));
+    h->pin = nullptr;
+    h->pin_bytes = 0;
+    const size_t cap = (need + 4095) / 4096 * 4096;
+    if (hipHostMalloc((void **)&h->pin, cap, hipHostMallocDefault) == hipSuccess) {
       h->pin_bytes = cap;
+    } else {  // none to be had: the copies below
+      (void)hipGetLastError();
+      h->pin = nullptr;
     }
+  }
+  if (need <= h->pin_bytes) {
     HIPCHK(launch_report(hist, h->hist_cap, row, first, (int)cnt, h->at<int>(h->off_ctl + 8), h->pin, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
     std::memcpy(out, h->pin + 1, bytes);

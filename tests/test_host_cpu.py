@@ -71,3 +71,18 @@ for chunk in (0, 8, 5, 50):
     assert np.all(f[:, 1] > f[:, 0])
     api.btdf_destroy(h)
 """ % (velocity,))
+
+
+def test_forces_without_pinned_memory(stand_in):
+    """Forces and histories are read by plain copies where no pinned host memory
+    is to be had."""
+    child(stand_in, """
+hip.host_hip_fail_pinned(1)
+h = handle(64, 48, [W.cylinder_body(30.0, 20.0, 8.0, 25)])
+for k in range(5):
+    api.btdf_step(h, 1)
+    assert api.btdf_forces(h).shape == (1, 3)
+api.btdf_step(h, 300)
+assert api.btdf_force_history(h, 400).shape == (305, 1, 3)
+api.btdf_destroy(h)
+""")
