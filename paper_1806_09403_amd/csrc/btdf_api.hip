@@ -23,6 +23,49 @@
 
 using namespace btdf;
 
+void btdf_report_pages::enter() {
+  std::lock_guard<std::mutex> lock(mu);
+  ++handles;
+}
+
+void btdf_report_pages::leave() {
+  std::lock_guard<std::mutex> lock(mu);
+  if (--handles) return;
+  if (base) (void)hipHostFree(base);
+  base = nullptr;
+  reads = 0;
+  refused = false;
+}
+
+double *btdf_report_pages::take() {
+  std::lock_guard<std::mutex> lock(mu);
+  if (!base) {
+    if (refused || ++reads < 2) return nullptr;
+    if (hipHostMalloc((void **)&base, kPages * kBytes, hipHostMallocPortable) != hipSuccess) {
+      (void)hipGetLastError();  // (not for the next launch to report)
+      base = nullptr;
+      refused = true;
+      return nullptr;
+    }
+  }
+  for (int k = 0; k < kPages; ++k)
+    if (!(taken >> k & 1)) {
+      taken |= 1u << k;
+      return reinterpret_cast<double *>(base + k * kBytes);
+    }
+  return nullptr;
+}
+
+void btdf_report_pages::give(double *page) {
+  std::lock_guard<std::mutex> lock(mu);
+  taken &= ~(1u << ((reinterpret_cast<char *>(page) - base) / kBytes));
+}
+
+btdf_report_pages &report_pages() {
+  static btdf_report_pages pages;
+  return pages;
+}
+
 namespace btdf {
 namespace host {
 
@@ -866,37 +909,37 @@ int check_flag(btdf_t *h) {
   return rc ? rc : flag_status(flag);
 }
 
-// most bytes of forces that come by the report kernel
-static constexpr size_t kReportBytes = 64 * 1024;
+// a page of the report kernel's memory for one read (null: none)
+struct ReportPage {
+  double *at;
+  ReportPage() : at(report_pages().take()) {}
+  ~ReportPage() {
+    if (at) report_pages().give(at);
+  }
+  ReportPage(const ReportPage &) = delete;
+  ReportPage &operator=(const ReportPage &) = delete;
+};
 
 // The body forces of cnt steps from step first (all in the ring) to out, and
-// the status of the run. Waits for the handle's stream. A few kilobytes come
-// with the flag in one launch that writes pinned memory, and one wait; as a
-// copy each, with a wait before and between, they were four round trips (a
-// loop of set_marker_velocity, step(1), forces on 97x61: 77 us a turn then,
+// the status of the run. Waits for the handle's stream. Up to a page of them
+// comes with the flag in one launch that writes pinned memory, and one wait;
+// as a copy each, with a wait before and between, they were four round trips
+// (a loop of set_marker_velocity, step(1), forces on 97x61: 77 us a turn then,
 // 29 now, of which btdf_set_marker_velocity's launch in the place of two
-// copies and a wait is a third).
+// copies and a wait is a third; reads of 1 / 100 / 1000 / 2700 rows of one
+// body: 36 / 49 / 52 / 110 us by copies, 17 / 18 / 27 / 70 by the kernel).
 static int read_forces(btdf_t *h, int64_t first, int64_t cnt, double *out) {
   const int row = 3 * h->nb();
-  const size_t bytes = (size_t)cnt * row * sizeof(double), need = bytes + sizeof(double);
+  const size_t bytes = (size_t)cnt * row * sizeof(double);
   const double *hist = h->at<double>(h->off_hist);
-  if (need <= kReportBytes && ++h->reports > 1 && h->pin_bytes < need) {
-    if (h->pin) HIPCHK(hipHostFree(h->pin));
-    h->pin = nullptr;
-    h->pin_bytes = 0;
-    const size_t cap = (need + 4095) / 4096 * 4096;
-    if (hipHostMalloc((void **)&h->pin, cap, hipHostMallocDefault) == hipSuccess) {
-      h->pin_bytes = cap;
-    } else {  // none to be had: the copies below
-      (void)hipGetLastError();
-      h->pin = nullptr;
+  if (bytes + sizeof(double) <= btdf_report_pages::kBytes) {
+    const ReportPage page;
+    if (page.at) {
+      HIPCHK(launch_report(hist, h->hist_cap, row, first, (int)cnt, h->at<int>(h->off_ctl + 8), page.at, h->stream));
+      HIPCHK(hipStreamSynchronize(h->stream));
+      std::memcpy(out, page.at + 1, bytes);
+      return flag_status((int)page.at[0]);
     }
-  }
-  if (need <= h->pin_bytes) {
-    HIPCHK(launch_report(hist, h->hist_cap, row, first, (int)cnt, h->at<int>(h->off_ctl + 8), h->pin, h->stream));
-    HIPCHK(hipStreamSynchronize(h->stream));
-    std::memcpy(out, h->pin + 1, bytes);
-    return flag_status((int)h->pin[0]);
   }
   HIPCHK(hipStreamSynchronize(h->stream));
   for (int64_t k = 0; k < cnt;) {
@@ -1198,7 +1241,6 @@ int destroy_impl(btdf_t *h) {
   if (h->fork_ev) (void)hipEventDestroy(h->fork_ev);
   if (h->join_ev) (void)hipEventDestroy(h->join_ev);
   h->tev.release();
-  if (h->pin) (void)hipHostFree(h->pin);
   if (h->ws && h->ws_owned) (void)hipFree(h->ws);
   delete h;
   return rc;

@@ -7,6 +7,7 @@
 
 #include <cstdint>
 #include <exception>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -19,6 +20,39 @@
     hipError_t e_ = (call);                                                                     \
     if (e_ != hipSuccess) return btdf::host::fail(BTDF_EDEVICE, "%s: %s", #call, hipGetErrorString(e_)); \
   } while (0)
+
+// Pinned host memory that the force reads' report kernel writes, shared by
+// all handles of the process: kPages pages in one allocation, made by the
+// second read of any handle (a program that reads once does not pay for it)
+// and given back with the last handle. A read holds a page for its own
+// length; where all are taken (more threads reading at once) or the memory is
+// not to be had, it goes by copies. (A buffer per handle, grown as needed,
+// cost 64 cases of a batch 1.1 ms in their second read and 12.5 ms when they
+// were destroyed, and a history longer than any before up to 0.5 ms.)
+class btdf_report_pages {
+ public:
+  static constexpr int kPages = 4;
+  static constexpr size_t kBytes = 64 * 1024;
+  void enter();
+  void leave();
+  double *take();  // null: none
+  void give(double *page);
+
+ private:
+  std::mutex mu;
+  char *base = nullptr;
+  unsigned taken = 0;
+  int handles = 0, reads = 0;
+  bool refused = false;  // not asked for again until the last handle has gone
+};
+btdf_report_pages &report_pages();
+// a handle's share in them
+struct btdf_report_user {
+  btdf_report_user() { report_pages().enter(); }
+  ~btdf_report_user() { report_pages().leave(); }
+  btdf_report_user(const btdf_report_user &) = delete;
+  btdf_report_user &operator=(const btdf_report_user &) = delete;
+};
 
 // HIP events of the timed stepping calls: created on first use and kept
 // until the handle is destroyed, so timing a run neither creates nor
@@ -150,11 +184,7 @@ struct btdf_sim {
   hipStream_t side = nullptr;
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
   btdf_event_pool tev;  // events of the timed stepping calls
-  // pinned host memory the force calls' report kernel writes (from the second
-  // such call on: a program that asks once does not pay for it)
-  double *pin = nullptr;
-  size_t pin_bytes = 0;
-  int reports = 0;
+  btdf_report_user reports;
 
   int nb() const { return (int)cx.size(); }
   bool any_moving() const {

@@ -18,11 +18,12 @@ enum { kOk = 0, kOutOfMemory = 2, kMax = 1 << 16 };
 
 /* per executed step launch: entries, workgroups, tiles stepped, tiles stepped twice */
 static int found[kMax][4], n_found;
-static int pinned_calls, pinned_fails, sticky;
+static int pinned_calls, pinned_live, pinned_fails, sticky;
 static graph *recording;
 
 int host_hip_steps(const int **out) { *out = &found[0][0]; return n_found; }
 int host_hip_pinned_calls(void) { return pinned_calls; }
+int host_hip_pinned_live(void) { return pinned_live; }
 void host_hip_fail_pinned(int on) { pinned_fails = on; }
 
 static void run(const launch *l) {
@@ -77,9 +78,10 @@ int hipHostMalloc(void **p, size_t n, unsigned flags) {
   (void)flags;
   ++pinned_calls;
   *p = pinned_fails ? NULL : calloc(1, n);
+  pinned_live += *p != NULL;
   return *p ? kOk : (sticky = kOutOfMemory);
 }
-int hipHostFree(void *p) { free(p); return kOk; }
+int hipHostFree(void *p) { pinned_live -= p != NULL; free(p); return kOk; }
 int hipGetLastError(void) { const int e = sticky; sticky = 0; return e; }
 int hipGetDevice(int *d) { *d = 0; return kOk; }
 int hipMemcpy(void *d, const void *s, size_t n, int kind) { (void)kind; memcpy(d, s, n); return kOk; }

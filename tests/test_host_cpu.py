@@ -86,3 +86,41 @@ api.btdf_step(h, 300)
 assert api.btdf_force_history(h, 400).shape == (305, 1, 3)
 api.btdf_destroy(h)
 """)
+
+
+def test_pinned_memory_is_made_once_and_given_back(stand_in):
+    """Reads of any length, by any number of handles and threads at once, share
+    one allocation, which goes with the last handle."""
+    child(stand_in, """
+import threading
+for turn in range(2):
+    calls = hip.host_hip_pinned_calls()
+    hs = [handle(48, 40, [W.cylinder_body(20.0, 20.0, 8.0, 25)] * (1 + k % 3)) for k in range(12)]
+
+    def read(h, nb):
+        for n in (1, 2, 30, 90, 400, 1100, 2000, 3):
+            api.btdf_step(h, n)
+            assert api.btdf_forces(h).shape == (nb, 3)
+            assert api.btdf_force_history(h, n).shape == (n, nb, 3)
+
+    def every(some):
+        for h in some:
+            read(h, api.btdf_forces(h).shape[0])
+
+    threads = [threading.Thread(target=every, args=(hs[k::6],)) for k in range(6)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert hip.host_hip_pinned_calls() == calls + 1, hip.host_hip_pinned_calls() - calls
+    for h in hs:
+        assert hip.host_hip_pinned_live() == 1
+        api.btdf_destroy(h)
+    assert hip.host_hip_pinned_live() == 0
+h = handle(48, 40, [W.cylinder_body(20.0, 20.0, 8.0, 25)])
+api.btdf_step(h, 5)
+calls = hip.host_hip_pinned_calls()
+api.btdf_force_history(h, 5)
+assert hip.host_hip_pinned_calls() == calls   # (a single read does not pay for it)
+api.btdf_destroy(h)
+""")
