@@ -1,7 +1,8 @@
 /* host_hip.c -- the HIP runtime calls of libbtdf without a GPU, preloaded by
  * test_host_cpu.py: device memory is host memory, kernels do nothing, and a
  * launch of the one-launch step is looked over where it would run (in a graph:
- * at every replay) and its findings kept for the test to read. */
+ * at every replay) and its findings kept for the test to read, as are the names
+ * of the kernels that would run. */
 #define _GNU_SOURCE
 #include <dlfcn.h>
 #include <stdint.h>
@@ -11,7 +12,7 @@
 typedef struct { uint32_t x, y, z; } dim3;
 typedef struct { int t0, t1, m0, m1; } item;             /* StepItem */
 typedef struct { const item *items; int count; } work;   /* StepWork */
-typedef struct { int is_step; work w; uint32_t grid; } launch;
+typedef struct { int is_step; work w; uint32_t grid; const char *name; } launch;
 typedef struct { launch *l; int n; } graph;
 
 enum { kOk = 0, kOutOfMemory = 2, kMax = 1 << 16 };
@@ -20,13 +21,22 @@ enum { kOk = 0, kOutOfMemory = 2, kMax = 1 << 16 };
 static int found[kMax][4], n_found;
 static int pinned_calls, pinned_live, pinned_fails, sticky;
 static graph *recording;
+static const char *ran[kMax];
+static int n_ran;
 
 int host_hip_steps(const int **out) { *out = &found[0][0]; return n_found; }
 int host_hip_pinned_calls(void) { return pinned_calls; }
 int host_hip_pinned_live(void) { return pinned_live; }
+/* executed launches of kernels whose name holds part */
+int host_hip_launched(const char *part) {
+  int n = 0;
+  for (int k = 0; k < n_ran; ++k) n += strstr(ran[k], part) != NULL;
+  return n;
+}
 void host_hip_fail_pinned(int on) { pinned_fails = on; }
 
 static void run(const launch *l) {
+  if (n_ran < kMax) ran[n_ran++] = l->name;
   if (!l->is_step || n_found == kMax) return;
   static unsigned char seen[1 << 20];
   memset(seen, 0, sizeof seen);
@@ -49,7 +59,8 @@ int hipLaunchKernel(const void *fn, dim3 grid, dim3 block, void **args, size_t s
   (void)block, (void)shared, (void)stream;
   Dl_info d;
   launch l = {0};
-  if (dladdr(fn, &d) && d.dli_sname && strstr(d.dli_sname, "step_kernel")) {
+  l.name = dladdr(fn, &d) && d.dli_sname ? d.dli_sname : "?";
+  if (strstr(l.name, "step_kernel")) {
     l.is_step = 1;
     l.w = *(const work *)args[3];
     l.grid = grid.x;

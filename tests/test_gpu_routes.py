@@ -1,0 +1,32 @@
+"""Rules that send the same work to one kernel or another: on both sides of
+each the results are the same bits."""
+import numpy as np
+import pytest
+
+import btdf_workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("precision", [4, 8])
+@pytest.mark.parametrize("n,far,passes", [(31, (64, 65), 2), (64, (96, 97), 4), (100, (128, 129), 6), (17, (64, 65), 1),
+                                          (50, (63, 70), 1)])
+def test_bodies_formed_whole_or_by_launches_over_all_markers(n, far, passes, precision):
+    """A far body of one marker more changes the kernels that form the forces
+    of a first one (passes = 1: the implicit method), whose first steps, before
+    the far one's flow reaches it, do not change by a bit."""
+    from paper_1806_09403_amd import Sim, _lib
+    out = []
+    for m in far:
+        s = Sim(260, 90, 0.8, W.ROMA3, 1.9, W.FULLY_PERIODIC, init=(1.0, 0.02, 0.01), precision=precision)
+        for x, k in ((50.3, n), (190.6, m)):
+            b = W.cylinder_body(x, 45.2, 1.2 * k / np.pi, k, np.random.default_rng(k).uniform(-0.01, 0.01, (k, 2)))
+            s.add_body(b.xy, b.uv, b.cx, b.cy, b.ds)
+        s.set_option(*((_lib.OPT_FORCING_METHOD, 1) if passes == 1 else (_lib.OPT_FORCING_PASSES, passes)))
+        s.step(7)
+        d = s.marker_data()
+        out.append([s.populations()[:, :, :100], s.force_history(7)[:, 0]] + [v[:n] for v in d.values()])
+        s.close()
+    assert np.any(out[0][1])
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)

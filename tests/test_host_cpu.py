@@ -17,8 +17,8 @@ import btdf_workloads as W
 from paper_1806_09403_amd import _lib, api
 hip = ctypes.CDLL(None)
 
-def handle(nx, ny, bodies, precision=8):
-    h = api.btdf_create(nx, ny, 0.8, W.COS4, 2.6, W.FULLY_PERIODIC, precision=precision)
+def handle(nx, ny, bodies, precision=8, kind=W.COS4):
+    h = api.btdf_create(nx, ny, 0.8, kind, 2.6, W.FULLY_PERIODIC, precision=precision)
     for b in bodies:
         api.btdf_add_body(h, b.xy, None, b.cx, b.cy, b.ds)
     return h
@@ -124,3 +124,25 @@ api.btdf_force_history(h, 5)
 assert hip.host_hip_pinned_calls() == calls   # (a single read does not pay for it)
 api.btdf_destroy(h)
 """)
+
+
+@pytest.mark.parametrize("n,bodies,passes,whole", [
+    (64, 1, 2, True), (65, 1, 2, False), (80, 1, 3, True), (128, 1, 3, False), (128, 1, 6, True), (129, 1, 8, False),
+    (256, 1, 8, False), (256, 4, 3, False), (64, 1, 1, True), (65, 1, 1, False), (200, 1, 1, False),
+    (100, 60, 2, True), (100, 60, 1, True), (200, 160, 2, True)])
+def test_bodies_are_formed_whole_where_that_is_faster(stand_in, n, bodies, passes, whole):
+    """One workgroup per body for small bodies, and for many; launches over all
+    markers for few large bodies. (passes = 1: the implicit method.)"""
+    child(stand_in, """
+n, bodies, passes, whole = %r
+g = int(1.2 * n / np.pi) + 20
+k = int(np.ceil(bodies ** 0.5))
+h = handle(k * g, k * g, [W.cylinder_body((i %% k + 0.5) * g, (i // k + 0.5) * g, 1.2 * n / np.pi, n)
+                          for i in range(bodies)], kind=W.ROMA3)
+api.btdf_set_option(h, *((_lib.OPT_FORCING_METHOD, 1) if passes == 1 else (_lib.OPT_FORCING_PASSES, passes)))
+api.btdf_set_option(h, _lib.OPT_TEMPORAL_BLOCKING, 0)
+api.btdf_step(h, 3)
+ran = [hip.host_hip_launched(b) for b in (b"body_kernel", b"9ib_kernel", b"ib_pass_kernel", b"idf_kernel")]
+want = [3, 0, 0, 0] if whole else [0, 3, 3 * (passes - 1), 3 * (passes == 1)]
+assert ran == want, (ran, want)
+""" % ((n, bodies, passes, whole),))
