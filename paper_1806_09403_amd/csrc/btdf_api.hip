@@ -546,7 +546,7 @@ bool bodies_apart(btdf_t *h) {
 // step.
 void step_items(btdf_t *h, int least) {
   h->work.clear();
-  h->n_work[0] = h->n_work[1] = h->n_work_forced[0] = h->n_work_forced[1] = 0;
+  for (int k = 0; k < 2; ++k) h->n_work[k] = h->n_work_forced[k] = h->work_most[k] = 0;
   if (!variant_has_step(h->variant) || h->owner || h->ntx > 0xffff || h->nty > 0x7fff) return;
   for (int near = 0; near < 2; ++near) {
     const size_t start = h->work.size();
@@ -556,6 +556,7 @@ void step_items(btdf_t *h, int least) {
     for (int k = 0; k < n; ++k) {
       const int t = tile(k), m0 = h->tile_off[t], m1 = h->tile_off[t + 1];
       if (m1 > m0) h->work.push_back({code(t), -1, m0, m1});
+      h->work_most[near] = std::max(h->work_most[near], m1 - m0);
     }
     h->n_work_forced[near] = (int)(h->work.size() - start);
     bool half = false;
@@ -979,7 +980,8 @@ StepWork step_work(const btdf_t *h, bool near) {
 // whether a step over these tiles goes through the step kernel's work items
 static bool few_tiles(const btdf_t *h, bool near) {
   return variant_has_step(h->variant) && h->plane * h->prec < (1LL << 32) && h->n_work[near] > 0 &&
-         h->n_work[near] <= kStepMaxWork && h->n_work_forced[near] <= kStepMaxForced;
+         h->n_work[near] <= kStepMaxWork && h->n_work_forced[near] <= kStepMaxForced &&
+         (h->work_most[near] <= kStepMaxMarkers || h->n_work_forced[near] >= kStepManyForced);
 }
 
 bool one_launch(const btdf_t *h, bool near) {

@@ -141,6 +141,7 @@ struct btdf_sim {
   // pass's near tiles
   std::vector<btdf::StepItem> work;
   int n_work[2] = {0, 0}, n_work_forced[2] = {0, 0};  // entries, and those with markers
+  int work_most[2] = {0, 0};                          // most markers of one entry
   int n_groups() const {
     int k = 0;
     for (int i = 0; i < btdf::kLevels; ++i) k += n_grp[i];
@@ -260,6 +261,15 @@ constexpr int kSquareBand = 32;
 // markers 37.2 against 45.2 us on 2000x1400 and equal at 88 on 3000x2000
 // (11 800 workgroups; all FP32, FP64 alike).
 constexpr int kStepMaxForced = 1536, kStepMaxWork = 8192;
+// Most markers of a tile, where fewer tiles than kStepManyForced have any. A
+// body traced with many markers per node makes a few tiles' chains the step's
+// length, and each node of such a tile reads its own markers' values where the
+// lattice kernel's waves read one marker's for all: per step, one launch / two,
+// FP32 (FP64 alike), 200x120 with one body of D = 20, 207 markers in a tile
+// 28.3 / 29.1 us, 302 47.7 / 40.6, 377 60.8 / 48.8; of D = 64, 285 38.6 / 38.9,
+// 360 54.6 / 46.5. With 234 tiles of 279 (1024^2, 31 bodies) 38.8 / 51.5, of
+// 604 93.3 / 95.6.
+constexpr int kStepMaxMarkers = 288, kStepManyForced = 128;
 std::string forcing_setup(btdf_t *h);
 LbmParams make_params(const btdf_t *h);
 IbParams make_ib(const btdf_t *h);

@@ -146,3 +146,15 @@ ran = [hip.host_hip_launched(b) for b in (b"body_kernel", b"9ib_kernel", b"ib_pa
 want = [3, 0, 0, 0] if whole else [0, 3, 3 * (passes - 1), 3 * (passes == 1)]
 assert ran == want, (ran, want)
 """ % ((n, bodies, passes, whole),))
+
+
+@pytest.mark.parametrize("n,one", [(63, True), (700, True), (800, False), (4000, False)])
+def test_steps_of_tiles_with_very_many_markers_take_two_launches(stand_in, n, one):
+    """(700 markers on D = 20: 264 in a tile; 800: 302.)"""
+    child(stand_in, """
+n, one = %r
+h = handle(200, 120, [W.cylinder_body(70.3, 60.2, 20.0, n)])
+api.btdf_step(h, 4)
+ran = [hip.host_hip_launched(b) for b in (b"11step_kernel", b"9ib_kernel", b"10lbm_kernel")]
+assert ran == ([4, 0, 0] if one else [0, 4, 4]), ran
+""" % ((n, one),))
