@@ -19,12 +19,14 @@ enum { kOk = 0, kOutOfMemory = 2, kMax = 1 << 16 };
 
 /* per executed step launch: entries, workgroups, tiles stepped, tiles stepped twice */
 static int found[kMax][4], n_found;
+static work last_step;
 static int pinned_calls, pinned_live, pinned_fails, sticky;
 static graph *recording;
 static const char *ran[kMax];
 static int n_ran;
 
 int host_hip_steps(const int **out) { *out = &found[0][0]; return n_found; }
+int host_hip_last_step(const int **items) { *items = (const int *)last_step.items; return last_step.count; }
 int host_hip_pinned_calls(void) { return pinned_calls; }
 int host_hip_pinned_live(void) { return pinned_live; }
 /* executed launches of kernels whose name holds part */
@@ -38,6 +40,7 @@ void host_hip_fail_pinned(int on) { pinned_fails = on; }
 static void run(const launch *l) {
   if (n_ran < kMax) ran[n_ran++] = l->name;
   if (!l->is_step || n_found == kMax) return;
+  last_step = l->w;
   static unsigned char seen[1 << 20];
   memset(seen, 0, sizeof seen);
   int *f = found[n_found++];

@@ -158,3 +158,47 @@ api.btdf_step(h, 4)
 ran = [hip.host_hip_launched(b) for b in (b"11step_kernel", b"9ib_kernel", b"10lbm_kernel")]
 assert ran == ([4, 0, 0] if one else [0, 4, 4]), ran
 """ % ((n, one),))
+
+
+@pytest.mark.parametrize("nx,ny,bodies", [(300, 200, 1), (64, 48, 1), (420, 400, 9)])
+def test_consecutive_tiles_of_a_step_share_an_xcd(stand_in, nx, ny, bodies):
+    """Workgroup b runs on XCD b % 8: with BTDF_OPT_XCD_REMAP (the default)
+    those of an XCD take a run of consecutive tiles, among the tiles with markers
+    (which come first) and among the others; without it workgroups take the
+    tiles in order. The option takes effect at any time, and moves no tile
+    twice or none."""
+    child(stand_in, """
+nx, ny, bodies = %r
+h = handle(nx, ny, [W.cylinder_body(20.0 + 40 * (i %% 3), 20.0 + 40 * (i // 3), 12.0, 38) for i in range(bodies)])
+ntx = (nx + 31) // 32
+
+def items():
+    p = ctypes.POINTER(ctypes.c_int)()
+    n = hip.host_hip_last_step(ctypes.byref(p))
+    return np.ctypeslib.as_array(p, (n, 4)).copy()
+
+def tiles(part):   # in the order of the lattice
+    return [(t >> 16) * ntx + (t & 65535) for it in part for t in it[:2] if t >= 0]
+
+plain = None
+for remap in (None, 0, 1, 0):
+    if remap is not None:
+        api.btdf_set_option(h, _lib.OPT_XCD_REMAP, remap)
+    api.btdf_step(h, 2)
+    it = items()
+    nf = int(np.sum(it[:, 3] > it[:, 2]))
+    assert nf > 0 and np.all(it[:nf, 3] > it[:nf, 2])
+    whole = []
+    for first, last in ((0, nf), (nf, len(it))):
+        if remap == 0:
+            runs = [it[first:last]]
+        else:
+            runs = [it[[b for b in range(first, last) if b %% 8 == x]] for x in range(8)]
+        order = [t for r in runs for t in tiles(r)]
+        assert order == sorted(order), (remap, order)
+        whole.append(order)
+        assert remap == 0 or max(map(len, runs)) - min(map(len, runs)) <= 1
+    plain = plain or whole
+    assert whole == plain
+assert np.all(steps_found()[:, 2] == ntx * ((ny + 7) // 8)) and not np.any(steps_found()[:, 3])
+""" % ((nx, ny, bodies),))
