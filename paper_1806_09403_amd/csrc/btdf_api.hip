@@ -1053,12 +1053,29 @@ int run_step(btdf_t *h, const LbmParams &p, const IbParams &ib, const void *A, v
   return ok();
 }
 
+// Whether the matrices of the implicit method, read by one workgroup per body
+// in every step (idf_kernel; body b on XCD b % 8), and an XCD's share of the
+// populations together are about as large as its L2 of 4 MB. The step kernel's
+// stores stay in the L2, where the next step finds them, and would push the
+// matrices out; the lattice kernel's pass it by. Per step, marker records to
+// the step kernel / the lattice kernel, FP64: 352^2 with 4 bodies of 384
+// markers (3.4 MB) 59 / 42 us, 381^2 with 9 of 256 (3.7 MB) 29.4 / 24.3, 424^2
+// with 16 of 200 (3.9 MB) 30.1 / 25.6, 364^2 with 16 of 160 (2.8 MB) 24.5 /
+// 23.6; below, 318^2 with 9 of 200 (2.6 MB) 19.5 / 21.0, and above, 530^2 with
+// 25 of 200 (6.3 MB) 34.0 / 37.0.
+static bool matrices_fill_l2(const btdf_t *h) {
+  if (h->method != BTDF_FORCING_IMPLICIT || h->own_bodies) return false;
+  const double pops = 2.0 * 9.0 * (double)h->plane * h->prec / 8.0;
+  const double mats = (h->nb() + 7) / 8 * 8.0 * (double)h->max_body * h->max_body;
+  return pops + mats >= 2.7e6 && pops + mats <= 4.5e6;
+}
+
 // The lattice part of a step whose marker forces are in the marker records:
 // the step kernel, or over many tiles the lattice kernel. (The marker kernels
 // left the ring entry in slot word 0; the counter goes by word 1.)
 static int lattice_step(btdf_t *h, const LbmParams &p, const IbParams &ib, const void *A, void *B, bool near,
                         hipStream_t s) {
-  if (few_tiles(h, near)) {
+  if (few_tiles(h, near) && !matrices_fill_l2(h)) {
     HIPCHK(launch_step(h->prec, false, A, B, p, step_work(h, near), ib, StepLink{ib.Fx, ib.Fy, 1, 1, 0, 1}, MoveParams{}, s));
     return ok();
   }

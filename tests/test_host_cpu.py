@@ -202,3 +202,19 @@ for remap in (None, 0, 1, 0):
     assert whole == plain
 assert np.all(steps_found()[:, 2] == ntx * ((ny + 7) // 8)) and not np.any(steps_found()[:, 3])
 """ % ((nx, ny, bodies),))
+
+
+@pytest.mark.parametrize("g,bodies,n,precision,records", [(106, 3, 200, 8, True), (106, 4, 200, 8, False),
+                                                          (176, 2, 384, 8, False), (106, 5, 200, 8, True),
+                                                          (54, 9, 64, 8, True), (106, 3, 200, 4, True)])
+def test_matrices_that_fill_the_l2_keep_the_lattice_kernel(stand_in, g, bodies, n, precision, records):
+    """(Bodies per row of a square of them.)"""
+    child(stand_in, """
+g, k, n, precision, records = %r
+h = handle(k * g, k * g, [W.cylinder_body((i %% k + 0.5) * g, (i // k + 0.5) * g, 1.2 * n / np.pi, n)
+                          for i in range(k * k)], precision, W.ROMA3)
+api.btdf_set_option(h, _lib.OPT_FORCING_METHOD, 1)
+api.btdf_step(h, 2)
+ran = [hip.host_hip_launched(b) for b in (b"11step_kernel", b"10lbm_kernel")]
+assert ran == ([2, 0] if records else [0, 2]), ran
+""" % ((g, bodies, n, precision, records),))
