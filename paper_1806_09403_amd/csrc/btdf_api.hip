@@ -514,10 +514,12 @@ MoveParams make_move(const btdf_t *h, int from, int to) {
 // body_kernel takes 64 markers at a time: a further pass costs a body of 64
 // markers 1.1 us, of 128 1.6, of 256 4.0, against 3.3 for a launch over all
 // markers, and what comes before it 1, 6 and 13 us more than the marker kernel
-// does. So with few bodies it pays up to 64 markers, or 128 with passes enough;
-// with many the launches over all markers are bound by their bytes. Per step, launches of
-// their own / body_kernel, FP32 (FP64 alike): one body of 64 markers NF = 2
-// 12.5 / 11.5 us, implicit 12.7 / 11.5; of 128 NF = 2 12.8 / 16.7, NF = 5
+// does. So with few bodies it pays up to 64 markers (80 with the implicit
+// method, where it spares the matrices' launch), or 128 with passes enough;
+// with many bodies the launches over all markers are bound by their bytes. Per
+// step, launches of their own / body_kernel, FP32 (FP64 alike): one body of 64
+// markers NF = 2 12.5 / 11.5 us, implicit 12.7 / 11.5; of 80 implicit 13.1 /
+// 13.1 (31 of 75 on 1024^2 25.7 / 23.1); of 128 NF = 2 12.8 / 16.7, NF = 5
 // 22.9 / 21.4, implicit 15.3 / 18.7; of 256 NF = 3 15.9 / 30.5, NF = 12 43.6 /
 // 66.6, implicit 19.9 / 28.0; 100 bodies of 80 NF = 2 21.9 / 20.7, implicit
 // 24.9 / 21.4; of 192 NF = 3 43.9 / 45.2; 225 of 144 NF = 2 53.5 / 48.0.
@@ -528,7 +530,7 @@ bool bodies_apart(btdf_t *h) {
   int most = 0;
   for (int b = 0; b < h->nb(); ++b) most = std::max(most, h->off[b + 1] - h->off[b]);
   if (most > kBodyMax) return false;
-  const bool small = most <= 64 || (most <= 128 && !implicit && most <= 16 * (h->nf + 2));
+  const bool small = most <= std::min(128, 16 * (implicit ? 5 : h->nf + 2));
   if (!small && h->nm() < (most <= 128 ? kBodyMany : kBodyFull)) return false;
   h->max_body = most;
   if (implicit) return true;

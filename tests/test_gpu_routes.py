@@ -9,8 +9,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("precision", [4, 8])
-@pytest.mark.parametrize("n,far,passes", [(31, (64, 65), 2), (64, (96, 97), 4), (100, (128, 129), 6), (17, (64, 65), 1),
-                                          (50, (63, 70), 1)])
+@pytest.mark.parametrize("n,far,passes", [(31, (64, 65), 2), (64, (96, 97), 4), (100, (128, 129), 6), (17, (80, 81), 1),
+                                          (50, (63, 100), 1)])
 def test_bodies_formed_whole_or_by_launches_over_all_markers(n, far, passes, precision):
     """A far body of one marker more changes the kernels that form the forces
     of a first one (passes = 1: the implicit method), whose first steps, before

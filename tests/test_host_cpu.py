@@ -128,7 +128,7 @@ api.btdf_destroy(h)
 
 @pytest.mark.parametrize("n,bodies,passes,whole", [
     (64, 1, 2, True), (65, 1, 2, False), (80, 1, 3, True), (128, 1, 3, False), (128, 1, 6, True), (129, 1, 8, False),
-    (256, 1, 8, False), (256, 4, 3, False), (64, 1, 1, True), (65, 1, 1, False), (200, 1, 1, False),
+    (256, 1, 8, False), (256, 4, 3, False), (80, 1, 1, True), (81, 1, 1, False), (200, 1, 1, False),
     (100, 60, 2, True), (100, 60, 1, True), (200, 160, 2, True)])
 def test_bodies_are_formed_whole_where_that_is_faster(stand_in, n, bodies, passes, whole):
     """One workgroup per body for small bodies, and for many; launches over all
