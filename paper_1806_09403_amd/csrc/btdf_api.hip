@@ -298,6 +298,7 @@ void fused_lists(btdf_t *h) {
   h->n_near = 0;
   h->near.clear();
   h->rwin.clear();
+  h->beside = false;
   const int d = h->depth;
   if (d < 2) return;
   const int tx = h->tile_x, ty = h->tile_y, ntx = h->ntx, nty = h->nty, ntiles = ntx * nty;
@@ -522,7 +523,11 @@ MoveParams make_move(const btdf_t *h, int from, int to) {
 // 13.1 (31 of 75 on 1024^2 25.7 / 23.1); of 128 NF = 2 12.8 / 16.7, NF = 5
 // 22.9 / 21.4, implicit 15.3 / 18.7; of 256 NF = 3 15.9 / 30.5, NF = 12 43.6 /
 // 66.6, implicit 19.9 / 28.0; 100 bodies of 80 NF = 2 21.9 / 20.7, implicit
-// 24.9 / 21.4; of 192 NF = 3 43.9 / 45.2; 225 of 144 NF = 2 53.5 / 48.0.
+// 24.9 / 21.4; of 192 NF = 3 43.9 / 45.2; 225 of 144 NF = 2 53.5 / 48.0. Beside
+// a pass's large groups a launch more costs 5 us: one body of 126 on 1601^2
+// NF = 2 25.8 / 29.5, NF = 3 30.9 / 29.9, NF = 5 40.3 / 33.0, implicit 29.1 /
+// 31.1; 5 of 94 on 1200x1100 NF = 2 23.8 / 23.5, NF = 3 29.1 / 24.5, implicit
+// 25.6 / 24.2; one of 251 on 2000x800 NF = 5 38.6 / 45.5.
 constexpr int kBodyMany = 6000, kBodyFull = 32000;  // markers from which bodies of 65-128 and of more pay anyway
 bool bodies_apart(btdf_t *h) {
   const bool implicit = h->method == BTDF_FORCING_IMPLICIT;
@@ -530,7 +535,8 @@ bool bodies_apart(btdf_t *h) {
   int most = 0;
   for (int b = 0; b < h->nb(); ++b) most = std::max(most, h->off[b + 1] - h->off[b]);
   if (most > kBodyMax) return false;
-  const bool small = most <= std::min(128, 16 * (implicit ? 5 : h->nf + 2));
+  const int limit = h->beside ? 32 * (implicit ? 3 : h->nf) : 16 * (implicit ? 5 : h->nf + 2);
+  const bool small = most <= std::min(128, limit);
   if (!small && h->nm() < (most <= 128 ? kBodyMany : kBodyFull)) return false;
   h->max_body = most;
   if (implicit) return true;
@@ -679,7 +685,6 @@ void compute_layout(btdf_t *h) {
   o = align256(o + (h->nf > 1 ? 4 * (size_t)std::max(nm, 1) * sizeof(double) : 0));
   // implicit forcing: one inverse matrix per body; RKPM: nothing beyond the marker factors
   h->method_err = forcing_setup(h);
-  h->own_bodies = bodies_apart(h);
   h->off_moff = o;
   o = align256(o + h->minv_off.size() * sizeof(long long));
   h->off_minv = o;
@@ -690,6 +695,7 @@ void compute_layout(btdf_t *h) {
   // population buffer for the singly stepped tiles' intermediate state
   h->depth = pass_depth(h);
   fused_lists(h);
+  h->own_bodies = bodies_apart(h);
   h->off_fmap = o;
   o = align256(o + 2 * (size_t)max_tiles * sizeof(int));
   h->off_rwin = o;  // per map entry

@@ -218,3 +218,22 @@ api.btdf_step(h, 2)
 ran = [hip.host_hip_launched(b) for b in (b"11step_kernel", b"10lbm_kernel")]
 assert ran == ([2, 0] if records else [0, 2]), ran
 """ % ((g, bodies, n, precision, records),))
+
+
+@pytest.mark.parametrize("n,passes,whole", [(64, 2, True), (65, 2, False), (96, 3, True), (97, 3, False), (128, 4, True),
+                                            (129, 9, False), (96, 1, True), (97, 1, False)])
+def test_bodies_are_formed_whole_beside_a_blocked_pass(stand_in, n, passes, whole):
+    """There a launch more costs more. (passes = 1: the implicit method.)"""
+    child(stand_in, """
+n, passes, whole = %r
+h = handle(1100, 1000, [W.cylinder_body(500.0, 500.0, 1.2 * n / np.pi, n)], 4, W.ROMA3)
+api.btdf_set_option(h, *((_lib.OPT_FORCING_METHOD, 1) if passes == 1 else (_lib.OPT_FORCING_PASSES, passes)))
+assert api.btdf_get_option(h, _lib.OPT_STEPS_PER_PASS) == 5
+api.btdf_step(h, 10)
+ran = [hip.host_hip_launched(b) for b in (b"body_kernel", b"9ib_kernel")]
+assert ran == ([10, 0] if whole else [0, 10]), ran
+api.btdf_set_option(h, _lib.OPT_TEMPORAL_BLOCKING, 0)   # (and not without it)
+api.btdf_step(h, 1)
+ran = [hip.host_hip_launched(b) - k for b, k in zip((b"body_kernel", b"9ib_kernel"), ran)]
+assert ran == ([1, 0] if n <= min(128, 80 if passes == 1 else 16 * passes + 32) else [0, 1]), ran
+""" % ((n, passes, whole),))
