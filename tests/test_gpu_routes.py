@@ -30,3 +30,30 @@ def test_bodies_formed_whole_or_by_launches_over_all_markers(n, far, passes, pre
     assert np.any(out[0][1])
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("precision,depth", [(4, 5), (4, 4), (8, 3)])
+def test_passes_beside_the_near_tiles_with_every_remainder(precision, depth):
+    """Runs of depth .. 2 depth - 1 steps (one pass and each number of steps left
+    over, of two and three in passes of their own) and timed runs, which take
+    the same groups in turn, against single steps."""
+    from paper_1806_09403_amd import Sim, _lib
+
+    def run(blocking, go):
+        s = Sim(420, 300, 0.8, W.COS4, 2.6, W.FAR_FIELD, inflow=(0.03, 0.0), init=(1.0, 0.02, 0.0), precision=precision)
+        s.set_option(_lib.OPT_TEMPORAL_BLOCKING, blocking)
+        s.set_option(_lib.OPT_EDGE_TILES, 0)
+        for x, y, D, n in ((126.3, 150.2, 21.0, 66), (250.7, 90.4, 12.0, 100)):
+            b = W.cylinder_body(x, y, D, n)
+            s.add_body(b.xy, None, b.cx, b.cy, b.ds)
+        out = []
+        for n in range(depth, 2 * depth):
+            getattr(s, go)(n)
+            out += [s.populations(), s.force_history(n), *s.marker_data().values()]
+        s.close()
+        return out
+
+    want = run(0, "step")
+    for go in ("step", "step_timed_pass", "step_timed_split"):
+        for a, b in zip(run(depth, go), want):
+            assert np.array_equal(a, b), go
