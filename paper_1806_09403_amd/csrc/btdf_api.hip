@@ -1024,7 +1024,8 @@ static bool few_tiles(const btdf_t *h, bool near) {
 }
 
 bool one_launch(const btdf_t *h, bool near) {
-  return h->nm() > 0 && h->nf == 1 && h->method != BTDF_FORCING_IMPLICIT && few_tiles(h, near);
+  return h->nm() > 0 && h->nf == 1 && h->method != BTDF_FORCING_IMPLICIT && few_tiles(h, near) &&
+         (!near || h->n_work_forced[1] <= kStepMaxNear);
 }
 
 int run_step(btdf_t *h, const LbmParams &p, const IbParams &ib, const void *A, void *B, bool near, hipStream_t s,

@@ -252,15 +252,24 @@ constexpr long long kBlockMinNodes = 1ll << 20;
 constexpr int kDefaultDepth = 5;
 // width in tile columns of the bands down which groups two tiles tall are launched
 constexpr int kSquareBand = 32;
-// Most tiles with markers, and most workgroups, of a one-launch step: where
-// two launches in turn are as fast. Forming a marker in every tile it touches
+// Most tiles with markers, and most workgroups, of the step kernel, where two
+// launches in turn are as fast. Forming a marker in every tile it touches
 // costs 2.5 times the marker kernel's reads, so it pays only while tiles are
-// too few to fill the GPU: per step 17.6 us against 26.6 on 1024^2 with 31
-// cylinders of D = 24 (350 tiles), 42.8 against 44.1 on 2048^2 with 125 (1400,
-// blocked passes), 80.8 against 77.0 on 3072^2 with 280 (3100); without many
-// markers 37.2 against 45.2 us on 2000x1400 and equal at 88 on 3000x2000
-// (11 800 workgroups; all FP32, FP64 alike).
+// too few to fill the GPU. Per step, two launches / one, FP32 and FP64: 800^2
+// with one cylinder 17.9 / 10.4 us and 26.0 / 16.1; 1024^2 with 31 of D = 24
+// (350 tiles) 24.9 / 16.8 and 37.8 / 26.1, with 200 (1500) 27.4 / 24.7 and 40.1 /
+// 34.4; without many markers 2000x1400 46.0 / 32.1 and 81.7 / 79.8, 2500x1800
+// (9000 workgroups) 67.4 / 65.8 and 129.9 / 132.5, 3000x2000 87.8 / 89.7 and
+// equal at 172.
 constexpr int kStepMaxForced = 1536, kStepMaxWork = 8192;
+// Most tiles with markers among a pass's near tiles whose markers the step
+// kernel forms: beside the pass's groups every repeated read costs them time.
+// Per step, marker kernel and step kernel / one launch, FP32 and FP64: 2048^2
+// with 60 cylinders (480 tiles) equal at 33.7 us and 60.3, with 90 (643) 36.0 /
+// 36.5 and 59.8 / 62.0, with 125 (937) 38.8 / 40.7 and 62.6 / 64.2, with 200
+// (1434) 44.2 / 47.4 and 71.3 / 73.5; 2560^2 with 200 (1521) 53.4 / 59.6 and
+// 100.9 / 102.0; with few, 2000x800 with one (25) 20.2 / 15.1 and 27.1 / 23.9.
+constexpr int kStepMaxNear = 600;
 // Most markers of a tile, where fewer tiles than kStepManyForced have any. A
 // body traced with many markers per node makes a few tiles' chains the step's
 // length, and each node of such a tile reads its own markers' values where the

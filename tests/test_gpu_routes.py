@@ -57,3 +57,30 @@ def test_passes_beside_the_near_tiles_with_every_remainder(precision, depth):
     for go in ("step", "step_timed_pass", "step_timed_split"):
         for a, b in zip(run(depth, go), want):
             assert np.array_equal(a, b), go
+
+
+@pytest.mark.parametrize("precision,bodies", [(4, 49), (4, 121), (8, 121)])
+def test_near_steps_in_one_and_two_launches_beside_a_pass(precision, bodies):
+    """Few tiles with markers take a near step in one launch, more than 600 in
+    two: both as single steps without a pass, in and out of graphs."""
+    from paper_1806_09403_amd import Sim, _lib
+    k = int(bodies ** 0.5)
+
+    def run(blocking, chunk):
+        s = Sim(1210, 1100, 0.8, W.ROMA3, 1.9, W.FULLY_PERIODIC, init=(1.0, 0.02, 0.01), precision=precision)
+        s.set_option(_lib.OPT_TEMPORAL_BLOCKING, blocking)
+        s.set_option(_lib.OPT_GRAPH_CHUNK, chunk)
+        for i in range(bodies):
+            b = W.cylinder_body((i % k + 0.5) * 1210 / k, (i // k + 0.5) * 1100 / k, 24.0, 75,
+                                np.random.default_rng(i).uniform(-0.01, 0.01, (75, 2)))
+            s.add_body(b.xy, b.uv, b.cx, b.cy, b.ds)
+        assert (s.get_option(_lib.OPT_FORCED_TILES) > 600) == (bodies > 100)
+        s.step(32)
+        r = (s.populations(), s.force_history(32), *s.marker_data().values())
+        s.close()
+        return r
+
+    want = run(0, 0)
+    for chunk in (0, 15):
+        for a, b in zip(run(1, chunk), want):
+            assert np.array_equal(a, b), chunk

@@ -237,3 +237,20 @@ api.btdf_step(h, 1)
 ran = [hip.host_hip_launched(b) - k for b, k in zip((b"body_kernel", b"9ib_kernel"), ran)]
 assert ran == ([1, 0] if n <= min(128, 80 if passes == 1 else 16 * passes + 32) else [0, 1]), ran
 """ % ((n, passes, whole),))
+
+
+@pytest.mark.parametrize("bodies,one", [(25, True), (121, False)])
+def test_near_steps_of_many_tiles_take_two_launches(stand_in, bodies, one):
+    """(25 bodies: some 190 tiles with markers, 121: some 900.)"""
+    child(stand_in, """
+bodies, one = %r
+k = int(bodies ** 0.5)
+g = 1600 / k
+h = handle(1600, 1600, [W.cylinder_body((i %% k + 0.5) * g, (i // k + 0.5) * g, 24.0, 75) for i in range(bodies)], 4,
+           W.ROMA3)
+assert api.btdf_get_option(h, _lib.OPT_STEPS_PER_PASS) == 5
+assert (api.btdf_get_option(h, _lib.OPT_FORCED_TILES) <= 600) == one
+api.btdf_step(h, 10)
+ran = [hip.host_hip_launched(b) for b in (b"11step_kernel", b"9ib_kernel")]
+assert ran == ([10, 0] if one else [10, 10]), ran
+""" % ((bodies, one),))
