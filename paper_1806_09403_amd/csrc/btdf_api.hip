@@ -34,17 +34,16 @@ void btdf_report_pages::leave() {
   if (base) (void)hipHostFree(base);
   base = nullptr;
   reads = 0;
-  refused = false;
 }
 
 double *btdf_report_pages::take() {
   std::lock_guard<std::mutex> lock(mu);
   if (!base) {
-    if (refused || ++reads < 2) return nullptr;
+    if (++reads < 2) return nullptr;
     if (hipHostMalloc((void **)&base, kPages * kBytes, hipHostMallocPortable) != hipSuccess) {
       (void)hipGetLastError();  // (not for the next launch to report)
       base = nullptr;
-      refused = true;
+      reads = -64;  // (a capture on some thread may have forbidden it: not for good)
       return nullptr;
     }
   }

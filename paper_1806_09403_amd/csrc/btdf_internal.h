@@ -42,8 +42,7 @@ class btdf_report_pages {
   std::mutex mu;
   char *base = nullptr;
   unsigned taken = 0;
-  int handles = 0, reads = 0;
-  bool refused = false;  // not asked for again until the last handle has gone
+  int handles = 0, reads = 0;  // (reads since the memory was last to be asked for)
 };
 btdf_report_pages &report_pages();
 // a handle's share in them

@@ -84,6 +84,11 @@ for k in range(5):
     assert api.btdf_forces(h).shape == (1, 3)
 api.btdf_step(h, 300)
 assert api.btdf_force_history(h, 400).shape == (305, 1, 3)
+assert hip.host_hip_pinned_calls() == 1          # (not asked for in every read)
+hip.host_hip_fail_pinned(0)
+for k in range(80):
+    api.btdf_forces(h)
+assert hip.host_hip_pinned_calls() == 2 and hip.host_hip_pinned_live() == 1   # (nor given up for good)
 api.btdf_destroy(h)
 """)
 
