@@ -319,13 +319,20 @@ __global__ void init_uniform_kernel(T *__restrict__ A, LbmParams p, double r, do
 
 // Planes q0 .. q0 + gridDim.y of the populations <-> packed FP64 full values,
 // one plane after the other. Bound by memory (one population read or written
-// and one FP64 value the other way), so all planes go in one launch, and
-// where rows and both arrays allow it (V = 2: even rows, aligned pairs) a
-// thread moves two neighbours, one 16-byte access on the FP64 side; otherwise
-// one node. One pair per thread and no loop: the 8192^2 FP32 lattice takes
-// 1.12 ms (6.5 TB/s), 1.59 a node per thread, 1.22 in quadruples, 1.27 and
-// more with several per thread or a capped grid. (9 launches of a plane each
-// took 1.56 ms; on small lattices they cost 2.6 us apiece.)
+// and one FP64 value the other way), so all planes go in one launch (on small
+// lattices a launch costs 2.6 us). Where rows and both arrays allow it (V = 2:
+// even rows, aligned pairs) a thread moves two neighbours, one 16-byte access
+// on the FP64 side; otherwise four nodes 256 apart. Values handed out go by
+// nontemporal accesses, values taken in by plain ones (a row that is no whole
+// number of lines shares its last one with the next). To FP64 / back, us, nine
+// launches of a plane each / now: 8192^2 FP32 1580 / 1250 (5.8 TB/s) and 1380 /
+// 1150, FP64 1680 / 1540 and 1650 / 1560; 8191x8192 FP32 1575 / 1380 and 1430 /
+// 1275, FP64 1770 / 1630 and 1760 / 1675 (one node per thread: 2090, 1830,
+// 2055 and 2060); 1601^2 FP32 114 / 68 and 107 / 60.
+template <int V>
+constexpr int pops_nodes() {  // accesses per thread
+  return V == 1 ? 4 : 1;
+}
 template <typename T, int V>
 __global__ __launch_bounds__(256) void pops_to_f64_kernel(const T *__restrict__ A, LbmParams p, int q0,
                                                           double *__restrict__ out) {
@@ -336,14 +343,17 @@ __global__ __launch_bounds__(256) void pops_to_f64_kernel(const T *__restrict__ 
   const T *src = A + (long long)q * p.plane;
   double *dst = out + (long long)blockIdx.y * p.nx * p.ny;
   const double c = ref_c(q, p.urx, p.ury);
-  const unsigned k = blockIdx.x * 256u + threadIdx.x;
-  if (k >= n) return;
-  const unsigned y = k / w, x = (k - y * w) * V;
-  const vt v = __builtin_nontemporal_load(reinterpret_cast<const vt *>(src + (long long)y * p.pitch + x));
-  vd o;
 #pragma unroll
-  for (int u = 0; u < V; ++u) o[u] = (double)v[u] + c;
-  __builtin_nontemporal_store(o, reinterpret_cast<vd *>(dst + (long long)k * V));
+  for (int i = 0; i < pops_nodes<V>(); ++i) {
+    const unsigned k = (blockIdx.x * pops_nodes<V>() + i) * 256u + threadIdx.x;
+    if (k >= n) return;
+    const unsigned y = k / w, x = (k - y * w) * V;
+    const vt v = __builtin_nontemporal_load(reinterpret_cast<const vt *>(src + (long long)y * p.pitch + x));
+    vd o;
+#pragma unroll
+    for (int u = 0; u < V; ++u) o[u] = (double)v[u] + c;
+    __builtin_nontemporal_store(o, reinterpret_cast<vd *>(dst + (long long)k * V));
+  }
 }
 
 template <typename T, int V>
@@ -356,14 +366,17 @@ __global__ __launch_bounds__(256) void f64_to_pops_kernel(T *__restrict__ A, Lbm
   T *dst = A + (long long)q * p.plane;
   const double *src = in + (long long)blockIdx.y * p.nx * p.ny;
   const double c = ref_c(q, p.urx, p.ury);
-  const unsigned k = blockIdx.x * 256u + threadIdx.x;
-  if (k >= n) return;
-  const unsigned y = k / w, x = (k - y * w) * V;
-  const vd v = __builtin_nontemporal_load(reinterpret_cast<const vd *>(src + (long long)k * V));
-  vt o;
 #pragma unroll
-  for (int u = 0; u < V; ++u) o[u] = (T)(v[u] - c);
-  *reinterpret_cast<vt *>(dst + (long long)y * p.pitch + x) = o;
+  for (int i = 0; i < pops_nodes<V>(); ++i) {
+    const unsigned k = (blockIdx.x * pops_nodes<V>() + i) * 256u + threadIdx.x;
+    if (k >= n) return;
+    const unsigned y = k / w, x = (k - y * w) * V;
+    const vd v = *reinterpret_cast<const vd *>(src + (long long)k * V);
+    vt o;
+#pragma unroll
+    for (int u = 0; u < V; ++u) o[u] = (T)(v[u] - c);
+    *reinterpret_cast<vt *>(dst + (long long)y * p.pitch + x) = o;
+  }
 }
 
 // The body forces of cnt steps from step first (ring entries), and the
@@ -1249,11 +1262,15 @@ static bool pairs(int prec, const LbmParams &p, const void *pops, const void *f6
          (uintptr_t)f64 % 16 == 0;
 }
 
+static dim3 pops_grid(const LbmParams &p, bool v, int nq) {
+  const long long n = (long long)p.nx * p.ny / (v ? 2 : 1), per = 256 * (v ? pops_nodes<2>() : pops_nodes<1>());
+  return dim3((unsigned)((n + per - 1) / per), nq);
+}
+
 hipError_t launch_pops_to_f64(int prec, const void *A, const LbmParams &p, int q0, int nq, double *out,
                               hipStream_t s) {
   const bool v = pairs(prec, p, A, out);
-  const long long n = (long long)p.nx * p.ny / (v ? 2 : 1);
-  const dim3 g((unsigned)((n + 255) / 256), nq);
+  const dim3 g = pops_grid(p, v, nq);
   if (prec == 4 && v)
     hipLaunchKernelGGL((pops_to_f64_kernel<float, 2>), g, dim3(256), 0, s, (const float *)A, p, q0, out);
   else if (prec == 4)
@@ -1267,9 +1284,9 @@ hipError_t launch_pops_to_f64(int prec, const void *A, const LbmParams &p, int q
 
 hipError_t launch_f64_to_pops(int prec, void *A, const LbmParams &p, int q0, int nq, const double *in,
                               hipStream_t s) {
-  const bool v = pairs(prec, p, A, in);
-  const long long n = (long long)p.nx * p.ny / (v ? 2 : 1);
-  const dim3 g((unsigned)((n + 255) / 256), nq);
+  // (in FP64 pairs only in rows of whole lines: 8188^2 1760 us by pairs, 1670 by nodes)
+  const bool v = pairs(prec, p, A, in) && (prec == 4 || p.nx % 16 == 0);
+  const dim3 g = pops_grid(p, v, nq);
   if (prec == 4 && v)
     hipLaunchKernelGGL((f64_to_pops_kernel<float, 2>), g, dim3(256), 0, s, (float *)A, p, q0, in);
   else if (prec == 4)
