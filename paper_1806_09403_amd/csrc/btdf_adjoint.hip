@@ -199,7 +199,11 @@ int reverse_step(const Adj &X, const void *A, int64_t k, const double *hbar, int
 int recompute_segment(const Adj &X, int set, int64_t len, hipStream_t s) {
   const int prec = X.h->prec;
   const TileRange all{nullptr, 0, X.nt, 0};  // (neither the step counter nor the body forces)
-  const bool one = one_launch(X.h, false);
+  // (Beside the reversed steps of a large lattice the one-launch step's repeated
+  // reads cost them time. Forward run and sweep of 100 steps, recomputed in one
+  // launch / in two: 1000x800 FP64 with 25 bodies 8.44 / 8.65 ms, 1500x1000 FP32
+  // with 20 8.35 / 8.46, FP64 15.6 / 15.3, 2047x1025 FP32 with 60 12.6 / 12.3.)
+  const bool one = one_launch(X.h, false) && 18.0 * (double)X.h->plane * prec <= 1.28e8;
   for (int64_t k = 0; k < len; ++k) {
     LbmParams pk;
     IbParams ik;

@@ -84,3 +84,20 @@ def test_near_steps_in_one_and_two_launches_beside_a_pass(precision, bodies):
     for chunk in (0, 15):
         for a, b in zip(run(1, chunk), want):
             assert np.array_equal(a, b), chunk
+
+
+@pytest.mark.parametrize("nx,ny,precision", [(1400, 1200, 4), (1500, 1300, 4), (1000, 800, 8), (1100, 900, 8)])
+def test_gradients_recomputed_in_one_and_two_launches(nx, ny, precision):
+    """Up to 128 MB of populations a segment is recomputed in one launch a step,
+    beyond in two: both give the gradients of the run that keeps every state."""
+    from paper_1806_09403_amd import Sim
+    n, grads = 7, []
+    for every in (3, n):
+        s = Sim(nx, ny, 0.8, W.ROMA3, 1.9, W.CHANNEL, inflow=(0.03, 0.0), init=(1.0, 0.03, 0.0), precision=precision)
+        b = W.cylinder_body(0.3 * nx + 0.2, 0.5 * ny, 30.0, 94)
+        s.add_body(b.xy, np.random.default_rng(5).uniform(-0.01, 0.01, (94, 2)), b.cx, b.cy, b.ds)
+        grads.append(s.adjoint(n, np.random.default_rng(6).standard_normal((n, 1, 3)), every)[0])
+        s.close()
+    assert np.any(grads[0]["marker_uv"])
+    for k in grads[0]:
+        assert np.array_equal(grads[0][k], grads[1][k]), k
