@@ -255,7 +255,11 @@ int btdf_step(btdf_t *h, int64_t n);
 /* Same as btdf_step, but times the kernels with HIP events on the handle's
  * stream and writes, in milliseconds per step, the duration of the marker
  * kernel (*ms_ib, 0 if no bodies, or where a step is one launch that forms
- * the forces itself) and of the lattice launches (*ms_lbm).
+ * the forces itself; so in btdf_step_timed_split) and of the lattice launches
+ * (*ms_lbm). The results are those of btdf_step, the order of the launches of
+ * temporal blocking is not: where btdf_step runs a pass's large groups beside
+ * the near tiles' steps, the timed calls run them in turn, so that each has a
+ * duration of its own, and their steps take longer.
  * The events are created on the first timed call and kept until
  * btdf_destroy. Synchronising. */
 int btdf_step_timed(btdf_t *h, int64_t n, double *ms_ib, double *ms_lbm);
@@ -266,8 +270,8 @@ int btdf_step_timed(btdf_t *h, int64_t n, double *ms_ib, double *ms_lbm);
  * pass (over the passes taken, a two-step remainder pass included). */
 int btdf_step_timed_split(btdf_t *h, int64_t n, double *ms);
 
-/* Same as btdf_step, timing only the blocked pass of temporal blocking: HIP
- * events around the pass's launches alone (two per pass, on the stream the
+/* Same as btdf_step (launches in turn, as in btdf_step_timed), timing only the
+ * blocked pass of temporal blocking: HIP events around the pass's launches alone (two per pass, on the stream the
  * pass runs on), so the recording costs the steps little. *ms_pass: the
  * mean launch duration of the full-depth passes divided by the steps per
  * pass, in milliseconds per step (0 when no such pass ran: blocking off, or

@@ -262,10 +262,12 @@ void group_kinds(int variant, int prec, int d, int kind[kLevels]) {
 // tiles' steps: where those are few. They take a chain of small launches that
 // leaves most of the GPU idle, and wait only for the states of the groups that
 // border them; beside the chain the large groups cost little. Measured per
-// step, in turn and beside: 26.2 and 14.3 us on 2000x800 with one cylinder,
-// 36.2 and 32.3 on 2048^2 with 60 of D = 24, 42.8 and 40.2 with 125, equal at
-// 77 on 3072^2 with 280 (3100 tiles with markers; FP32, FP64 alike): with many
-// near tiles both fill the GPU and there is nothing to gain.
+// step, in turn / beside with near steps by the same rules, FP32 and FP64:
+// 20.6 / 14.0 us and 31.3 / 24.8 on 2000x800 with one cylinder, 36.8 / 32.9 and
+// 63.3 / 61.8 on 2048^2 with 60 of D = 24, 44.3 / 37.4 and 74.4 / 64.1 with
+// 125, 59.5 / 52.0 and 108 / 101 on 2560^2 with 200, equal at 77 and 143 on
+// 3072^2 with 280: with many near tiles both fill the GPU and there is nothing
+// to gain.
 bool pass_beside(const btdf_t *h, const std::vector<char> &near) {
   int kind[kLevels];
   group_kinds(h->variant, h->prec, h->depth, kind);
@@ -1872,7 +1874,7 @@ static int enqueue_deep(btdf_t *h, const LbmParams &p, const IbParams &ib, hipSt
     if ((rc = near_markers(h, p, ib, X[k], s, run))) return rc;
     HIPCHK(mark(2 * k + 2));
     if ((rc = near_step(h, p, ib, X[k], dst, s, run))) return rc;
-      HIPCHK(mark(2 * k + 3));
+    HIPCHK(mark(2 * k + 3));
   }
   h->cur ^= 1;
   h->steps += d;

@@ -272,7 +272,6 @@ struct MarkerUv {
   double u[kMax], v[kMax];
 };
 
-// rigid body motion, one workgroup per body after each step
 // One set of the bodies' places: [nb][4] theta, vx, vy, omega; centres;
 // markers and their velocities.
 struct BodyPlaces {

@@ -244,8 +244,12 @@ void cover_lists(const btdf_t *h, std::vector<int> &off, std::vector<int> &list)
 // implicit / RKPM matrices of the current bodies ("" or the reason they cannot be formed)
 constexpr int kMaxImplicitBody = 2048;
 constexpr int kMoveMargin = 2;  // nodes a moving marker may travel between tile-list rebuilds
-// smallest lattice that blocks by default: the 256-channel set (8 k to 520 k
-// nodes per case) ran at 11.4 GLUPS case by case unblocked, 8.2 blocked
+// Smallest lattice that blocks by default. Blocking pays from some 800 000
+// nodes (FP64 640 000); per step, single / blocked, one cylinder, FP32 and
+// FP64: 720^2 9.0 / 11.4 us and 14.0 / 14.8, 800^2 10.4 / 11.9 and 16.2 / 15.6,
+// 900^2 12.9 / 12.6 and 19.7 / 16.1, 1000^2 14.5 / 12.6 and 23.6 / 17.0. The
+// line is where it was set when both were slower and is part of the documented
+// defaults (1 step per pass below it); a smaller lattice blocks when asked to.
 constexpr long long kBlockMinNodes = 1ll << 20;
 // steps per pass by default on a single lattice, where the launch shape has them
 constexpr int kDefaultDepth = 5;

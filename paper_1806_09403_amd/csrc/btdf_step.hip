@@ -19,9 +19,10 @@
 // around it, and all form forces; without markers the two halves take a tile
 // each. (A ninth wave for the 20 ring nodes past 256 of a 4-point stencil
 // gains 2% on the 200x120 channel but costs a fifth of the workgroups a CU
-// holds: 57.8 -> 67.3 us a step on 2560^2 with 200 cylinders.) What a workgroup does is one 16-byte entry of a list made on the host
-// (forced tiles first, as they take longest), so nothing is looked up on the
-// way to the first population load.
+// holds: 57.8 -> 67.3 us a step on 2560^2 with 200 cylinders.) What a workgroup
+// does is one 16-byte entry of a list made on the host (forced tiles first, as
+// they take longest, and by XCD), so nothing is looked up on the way to the
+// first population load.
 #include "btdf_device.h"
 #include "btdf_launch.h"
 #include "btdf_tile.h"
