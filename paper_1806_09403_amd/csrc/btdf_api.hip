@@ -2210,7 +2210,7 @@ int btdf_forces(btdf_t *h, double *out, int cap_bodies) {
     const int nb = h->nb();
     if (h->steps == 0 || !h->ws) {
       for (int k = 0; k < 3 * nb; ++k) out[k] = 0.0;
-      return h->ws ? check_flag(h) : ok();
+      return h->ws && h->state_ok ? check_flag(h) : ok();  // (before that the workspace holds anything)
     }
     int rc = ensure_device(h);
     if (rc) return rc;
@@ -2228,7 +2228,7 @@ int btdf_force_history(btdf_t *h, double *out, int64_t max_steps, int64_t *n_wri
     const int nb = h->nb();
     if (!h->ws || nb == 0 || max_steps <= 0) {
       h->hist_read = h->steps;
-      return h->ws ? check_flag(h) : ok();
+      return h->ws && h->state_ok ? check_flag(h) : ok();  // (before that the workspace holds anything)
     }
     int rc = ensure_device(h);
     if (rc) return rc;

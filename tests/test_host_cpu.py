@@ -259,3 +259,21 @@ api.btdf_step(h, 10)
 ran = [hip.host_hip_launched(b) for b in (b"11step_kernel", b"9ib_kernel")]
 assert ran == ([10, 0] if one else [10, 10]), ran
 """ % ((bodies, one),))
+
+
+def test_forces_before_any_step_do_not_read_an_unwritten_workspace(stand_in):
+    """A workspace is the caller's memory, whatever it holds: before the state
+    is made there are no forces and no instability."""
+    child(stand_in, """
+h = handle(64, 48, [W.cylinder_body(30.0, 20.0, 8.0, 25)])
+n = api.btdf_workspace_bytes(h)
+ws = np.full(n + 256, 0xff, np.uint8)
+at = -(-ws.ctypes.data // 256) * 256
+api.btdf_bind_workspace(h, at, n)
+assert not np.any(api.btdf_forces(h))
+assert api.btdf_force_history(h, 0).shape[0] == 0
+assert api.btdf_force_history(h, 10).shape[0] == 0
+api.btdf_step(h, 3)
+assert api.btdf_force_history(h, 10).shape == (3, 1, 3)
+api.btdf_destroy(h)
+""")
